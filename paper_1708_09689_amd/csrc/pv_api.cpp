@@ -103,6 +103,7 @@ struct pv_lattice {
     // launch shapes per (dtype, log2 nb)
     pv_tuning tune[2][7] = {};
     pv_tuning tune_acc[2][7] = {};   // series steps (autotuned); kernel 0 = follow tune
+    bool searched[2][7] = {};        // the shapes come from pv_autotune, not from a caller's choice
     // generic stencils: the pattern struct of their generated kernels (empty
     // when a lane's row needs more slots than a kernel holds), and whether
     // sweeps take them (pv_lattice_set_codegen)
@@ -389,6 +390,9 @@ pv::SweepParams base_params(const pv_lattice* l, int dtype, int nb) {
     p.V = l->pot_mode ? l->V : nullptr;
     p.coef = l->d_coef;
     p.offs = l->d_offs;
+    p.real_diag = 1;
+    for (int o = 0; o < l->n_orb; ++o)
+        if (l->onsite[((size_t)o * l->n_orb + o) * 2 + 1] != 0.0) p.real_diag = 0;
     p.generic_stageable = generic_stageable(l);
     p.generic_side_halo = generic_side_halo(l);
     if (uses_codegen(l)) {
@@ -464,6 +468,18 @@ pv_status fill_traversal(pv_lattice* l, int dtype, int nb, pv::SweepParams& p) {
     p.acc_G8 = ta.groups_per_xcd;
     p.zero_row = l->d_zero;
     return PV_OK;
+}
+
+// Steps per pass of a run of `steps` Chebyshev steps on a 2D lattice, 0 for
+// one step per sweep.  A launch shape that the caller set asks for sweeps;
+// pv_autotune's shapes, chosen for single sweeps, do not.
+int plane_pass_steps(const pv_lattice* l, int dtype, int nb, int steps, bool kpm) {
+    static const bool env_off = std::getenv("PV_SWEEP") != nullptr && std::atoi(std::getenv("PV_SWEEP")) > 0;
+    if (env_off || l->dim != 2) return 0;
+    const int di = dtype == PV_C128 ? 0 : 1, ni = log2_nb(nb);
+    pv::SweepParams p = base_params(l, dtype, nb);
+    p.kernel = l->searched[di][ni] ? 0 : l->tune[di][ni].kernel;
+    return pv::plane_steps(p, steps, kpm);
 }
 
 }  // namespace
@@ -939,10 +955,29 @@ extern "C" pv_status pv_spmmv_noalloc(pv_lattice* l, int dtype, int nb, const vo
 // ---------------------------------------------------------------------------
 // KPM
 // ---------------------------------------------------------------------------
-extern "C" size_t pv_kpm_workspace_size(const pv_lattice* l, int dtype, int nb, int M) {
-    (void)M;
-    if (!l || !is_pow2(nb) || nb > PV_MAX_NB || (dtype != PV_C128 && dtype != PV_C64)) return 0;
+namespace {
+
+// Workspace of one sweep per step, the least that pv_kpm_moments takes.
+size_t kpm_sweep_bytes(const pv_lattice* l, int dtype, int nb) {
     return 2 * partial_bytes(l, nb) + 2 * vec_bytes(l, dtype, nb);
+}
+
+// Passes of several steps (2D lattices) need two vectors more, since a pass
+// does not overwrite its inputs, and the dots of kPlaneDots steps.
+constexpr int kPlaneDots = 60;
+size_t plane_dots_bytes(const pv_lattice* l, int dtype, int nb, int ts) {
+    return align_up((size_t)kPlaneDots * pv::plane_grid(base_params(l, dtype, nb), ts) * nb * 2 * sizeof(double));
+}
+size_t kpm_plane_bytes(const pv_lattice* l, int dtype, int nb, int ts) {
+    return kpm_sweep_bytes(l, dtype, nb) + 2 * vec_bytes(l, dtype, nb) + plane_dots_bytes(l, dtype, nb, ts);
+}
+
+}  // namespace
+
+extern "C" size_t pv_kpm_workspace_size(const pv_lattice* l, int dtype, int nb, int M) {
+    if (!l || !is_pow2(nb) || nb > PV_MAX_NB || (dtype != PV_C128 && dtype != PV_C64)) return 0;
+    const int ts = plane_pass_steps(l, dtype, nb, M / 2, true);
+    return ts ? kpm_plane_bytes(l, dtype, nb, ts) : kpm_sweep_bytes(l, dtype, nb);
 }
 
 namespace {
@@ -1029,18 +1064,58 @@ pv_status kpm_forward(pv_lattice* l, int dtype, int nb, int M, double a, double 
     return PV_OK;
 }
 
+// The moments in passes of ts steps.  W: four vectors; w_{k+ts-1}, w_{k+ts} of
+// a pass go to the pair that its inputs are not in.
+pv_status kpm_plane(pv_lattice* l, int dtype, int nb, int M, double a, double b, int ts, const void* r, double* mu,
+                    void* const W[4], double* dots, hipStream_t s) {
+    pv_status st;
+    pv::SweepParams p = base_params(l, dtype, nb);
+    if ((st = fill_traversal(l, dtype, nb, p)) != PV_OK) return st;
+    p.beta = b;
+    const int N = M / 2, grid = pv::plane_grid(p, ts);
+    const double invD = 1.0 / double(l->n_rows);
+    int n0 = 0;   // first step whose dots are not reduced yet
+    for (int k = 0, i = 0; k < N; k += ts, ++i) {
+        pv::PlanePass q{};
+        q.x = i ? W[2 * ((i - 1) & 1) + 1] : r;
+        q.z = i ? W[2 * ((i - 1) & 1)] : nullptr;
+        const bool last = k + ts >= N;
+        q.y1 = last ? nullptr : W[2 * (i & 1)];
+        q.y2 = last ? nullptr : W[2 * (i & 1) + 1];
+        q.partials = dots + (size_t)(k - n0) * grid * nb * 2;
+        q.alpha1 = (i ? 2.0 : 1.0) / a;
+        q.alpha = 2.0 / a;
+        q.levels = last ? N - k : ts;
+        PV_HIP(pv::launch_plane(p, ts, q, s));
+        const int done = last ? N : k + ts;
+        if (last || done - n0 + ts > kPlaneDots) {
+            PV_HIP(pv::launch_plane_moments(dots, grid, nb, n0, done - n0, mu, M, invD, s));
+            n0 = done;
+        }
+    }
+    return PV_OK;
+}
+
 }  // namespace
 
 extern "C" pv_status pv_kpm_moments(pv_lattice* l, int dtype, int nb, int M, double a, double b, const void* r,
                                     double* mu, void* work, size_t work_bytes, void* stream) {
     pv_status st;
     if ((st = check_kpm_args(l, dtype, nb, M, a, b, r, mu)) != PV_OK) return st;
-    const size_t need = pv_kpm_workspace_size(l, dtype, nb, M);
+    const size_t need = kpm_sweep_bytes(l, dtype, nb);
     if (!work || work_bytes < need) return fail(PV_ERR_WORKSPACE, "workspace %zu < %zu bytes", work_bytes, need);
     if ((st = ensure_device(l)) != PV_OK) return st;
     char* w = static_cast<char*>(work);
     void* A = w + 2 * partial_bytes(l, nb);
     void* B = static_cast<char*>(A) + vec_bytes(l, dtype, nb);
+    const int ts = plane_pass_steps(l, dtype, nb, M / 2, true);
+    if (ts && work_bytes >= kpm_plane_bytes(l, dtype, nb, ts)) {
+        const size_t vb = vec_bytes(l, dtype, nb);
+        char* v = static_cast<char*>(A);
+        void* const W[4] = {v, v + vb, v + 2 * vb, v + 3 * vb};
+        return kpm_plane(l, dtype, nb, M, a, b, ts, r, mu, W, reinterpret_cast<double*>(v + 4 * vb),
+                         static_cast<hipStream_t>(stream));
+    }
     // w_k in A for odd k, in B for even k (w_{k+1} overwrites w_{k-1})
     return kpm_forward(l, dtype, nb, M, a, b, r, mu, reinterpret_cast<double*>(w),
                        reinterpret_cast<double*>(w + partial_bytes(l, nb)),
@@ -1198,12 +1273,41 @@ namespace {
 // acc/out: Y = sum_k coef_k T_k(H~) X.  The accumulator `acc` is written by
 // the first sweep and updated by the later ones; the last sweep writes
 // acc + coef_K w_K to `out` (which may be X itself when K >= 2, since X is no
-// longer read by then).  W1, W2: two work vectors.
+// longer read by then).  W1, W2: two work vectors; W3, W4 (or NULL): two more,
+// with which 2D lattices take several steps per pass (a pass reads halos of
+// its inputs, so its outputs, `out` among them, are other buffers than those).
 pv_status run_series(pv_lattice* l, int dtype, int nb, double a, double b, int K, const double* coef,
-                     const void* X, void* acc, void* out, void* W1, void* W2, hipStream_t s) {
+                     const void* X, void* acc, void* out, void* W1, void* W2, void* W3, void* W4, hipStream_t s) {
     const int64_t n_elem = l->n_rows * nb;
     if (K == 0) {
         PV_HIP(pv::launch_scale_block(dtype, n_elem, X, coef[0], coef[1], out, s));
+        return PV_OK;
+    }
+    const int ts = W3 && W4 ? plane_pass_steps(l, dtype, nb, K, false) : 0;
+    if (ts && (K > ts || out != X)) {
+        pv::SweepParams p = base_params(l, dtype, nb);
+        pv_status st;
+        if ((st = fill_traversal(l, dtype, nb, p)) != PV_OK) return st;
+        p.beta = b;
+        void* const W[4] = {W1, W2, W3, W4};
+        std::vector<double> eta(2 * (ts + 1));
+        for (int k = 0, i = 0; k < K; k += ts, ++i) {
+            const bool last = k + ts >= K;
+            pv::PlanePass q{};
+            q.x = i ? W[2 * ((i - 1) & 1) + 1] : X;
+            q.z = i ? W[2 * ((i - 1) & 1)] : nullptr;
+            q.y1 = last ? nullptr : W[2 * (i & 1)];
+            q.y2 = last ? nullptr : W[2 * (i & 1) + 1];
+            q.acc_in = i ? acc : nullptr;
+            q.acc_out = last ? out : acc;
+            q.alpha1 = (i ? 2.0 : 1.0) / a;
+            q.alpha = 2.0 / a;
+            q.levels = last ? K - k : ts;
+            std::copy(coef, coef + 2, eta.begin());
+            std::copy(coef + 2 * (k + 1), coef + 2 * (k + q.levels + 1), eta.begin() + 2);
+            q.eta = eta.data();
+            PV_HIP(pv::launch_plane(p, ts, q, s));
+        }
         return PV_OK;
     }
     pv::SweepParams p = base_params(l, dtype, nb);
@@ -1292,9 +1396,17 @@ pv_status check_series_args(pv_lattice* l, int dtype, int nb, double a, double b
 
 }  // namespace
 
+namespace {
+// Work vectors of a series: two, and two more where passes of several steps
+// can serve it (fewer bytes than that are taken too, for one step per sweep).
+int series_vectors(const pv_lattice* l, int dtype, int nb) {
+    return plane_pass_steps(l, dtype, nb, 1 << 20, false) ? 4 : 2;
+}
+}  // namespace
+
 extern "C" size_t pv_cheb_series_workspace_size(const pv_lattice* l, int dtype, int nb) {
     if (!l || !is_pow2(nb) || nb > PV_MAX_NB || (dtype != PV_C128 && dtype != PV_C64)) return 0;
-    return 2 * vec_bytes(l, dtype, nb);
+    return series_vectors(l, dtype, nb) * vec_bytes(l, dtype, nb);
 }
 
 extern "C" pv_status pv_cheb_series(pv_lattice* l, int dtype, int nb, double a, double b, int K, const double* coef,
@@ -1308,12 +1420,13 @@ extern "C" pv_status pv_cheb_series(pv_lattice* l, int dtype, int nb, double a, 
     for (int k = 0; k <= K; ++k)
         if (!std::isfinite(coef[2 * k]) || !std::isfinite(coef[2 * k + 1]))
             return fail(PV_ERR_INVALID_ARG, "non-finite series coefficient %d", k);
-    const size_t need = pv_cheb_series_workspace_size(l, dtype, nb);
+    const size_t vb = vec_bytes(l, dtype, nb), need = 2 * vb;
     if (!work || work_bytes < need) return fail(PV_ERR_WORKSPACE, "workspace %zu < %zu bytes", work_bytes, need);
     if ((st = ensure_device(l)) != PV_OK) return st;
     char* w = static_cast<char*>(work);
-    return run_series(l, dtype, nb, a, b, K, coef, X, Y, Y, w, w + vec_bytes(l, dtype, nb),
-                      static_cast<hipStream_t>(stream));
+    const bool four = work_bytes >= 4 * vb;
+    return run_series(l, dtype, nb, a, b, K, coef, X, Y, Y, w, w + vb, four ? w + 2 * vb : nullptr,
+                      four ? w + 3 * vb : nullptr, static_cast<hipStream_t>(stream));
 }
 
 extern "C" pv_status pv_cheb_tp_coefficients(double a, double dt, int M, double* coef) {
@@ -1333,7 +1446,7 @@ extern "C" pv_status pv_cheb_tp_coefficients(double a, double dt, int M, double*
 
 extern "C" size_t pv_cheb_propagate_workspace_size(const pv_lattice* l, int dtype, int nb) {
     if (!l || !is_pow2(nb) || nb > PV_MAX_NB || (dtype != PV_C128 && dtype != PV_C64)) return 0;
-    return 3 * vec_bytes(l, dtype, nb);
+    return (1 + series_vectors(l, dtype, nb)) * vec_bytes(l, dtype, nb);
 }
 
 extern "C" pv_status pv_cheb_propagate(pv_lattice* l, int dtype, int nb, double a, double b, double dt, int M,
@@ -1342,7 +1455,7 @@ extern "C" pv_status pv_cheb_propagate(pv_lattice* l, int dtype, int nb, double 
     if ((st = check_series_args(l, dtype, nb, a, b)) != PV_OK) return st;
     if ((st = check_vec(psi, dtype, "psi")) != PV_OK) return st;
     if (M < 1 || nsteps < 0 || !std::isfinite(dt)) return fail(PV_ERR_INVALID_ARG, "need M >= 1, nsteps >= 0");
-    const size_t need = pv_cheb_propagate_workspace_size(l, dtype, nb);
+    const size_t need = 3 * vec_bytes(l, dtype, nb);
     if (!work || work_bytes < need) return fail(PV_ERR_WORKSPACE, "workspace %zu < %zu bytes", work_bytes, need);
     if ((st = ensure_device(l)) != PV_OK) return st;
     std::vector<double> coef(2 * (M + 1));
@@ -1360,12 +1473,16 @@ extern "C" pv_status pv_cheb_propagate(pv_lattice* l, int dtype, int nb, double 
     void* W1 = w;
     void* W2 = w + vb;
     void* ACC = w + 2 * vb;
+    void* W3 = work_bytes >= 5 * vb ? w + 3 * vb : nullptr;
+    void* W4 = work_bytes >= 5 * vb ? w + 4 * vb : nullptr;
     hipStream_t s = static_cast<hipStream_t>(stream);
     for (int step = 0; step < nsteps; ++step) {
         if (M >= 2) {
-            if ((st = run_series(l, dtype, nb, a, b, M, coef.data(), psi, ACC, psi, W1, W2, s)) != PV_OK) return st;
+            if ((st = run_series(l, dtype, nb, a, b, M, coef.data(), psi, ACC, psi, W1, W2, W3, W4, s)) != PV_OK)
+                return st;
         } else {
-            if ((st = run_series(l, dtype, nb, a, b, M, coef.data(), psi, ACC, ACC, W1, W2, s)) != PV_OK) return st;
+            if ((st = run_series(l, dtype, nb, a, b, M, coef.data(), psi, ACC, ACC, W1, W2, nullptr, nullptr, s)) != PV_OK)
+                return st;
             PV_HIP(pv::launch_copy(ACC, psi, (size_t)l->n_rows * nb * elem_bytes(dtype), s));
         }
     }
@@ -1562,6 +1679,7 @@ extern "C" pv_status pv_lattice_set_tuning(pv_lattice* l, int dtype, int nb, con
     if (t && (st = check_tuning(dtype, *t)) != PV_OK) return st;
     l->tune[dtype == PV_C128 ? 0 : 1][log2_nb(nb)] = t ? *t : z;
     l->tune_acc[dtype == PV_C128 ? 0 : 1][log2_nb(nb)] = z;   // series steps follow the set shape
+    l->searched[dtype == PV_C128 ? 0 : 1][log2_nb(nb)] = false;
     return PV_OK;
 }
 
@@ -1631,6 +1749,7 @@ extern "C" pv_status pv_autotune(pv_lattice* l, int dtype, int nb, const char* c
             check_tuning(dtype, ca) == PV_OK) {
             slot = c;
             slot_acc = ca;
+            l->searched[di][ni] = true;
             if (out) *out = c;
             if (ms_out) *ms_out = 0.0;
             return PV_OK;
@@ -1773,6 +1892,7 @@ extern "C" pv_status pv_autotune(pv_lattice* l, int dtype, int nb, const char* c
     }
     slot = best;
     slot_acc = best_acc;
+    l->searched[di][ni] = true;
     if (cache_path) cache_append(cache_path, key, best, best_acc, best_ms);
     if (out) *out = best;
     if (ms_out) *ms_out = best_ms;
@@ -1923,7 +2043,7 @@ extern "C" pv_status pv_chebfd(pv_lattice* l, int dtype, int bw, int nblk, doubl
         // 1. filter every block: Y_b = p(H~) X_b
         for (int bb = 0; bb < nblk; ++bb)
             if ((st = run_series(l, dtype, bw, a, b, degree, coef.data(), blk(Xc, bb), blk(Yb, bb), blk(Yb, bb),
-                                 w + Lw.S1, w + Lw.S2, s)) != PV_OK)
+                                 w + Lw.S1, w + Lw.S2, nullptr, nullptr, s)) != PV_OK)
                 return st;
         // 2. orthonormalise: Cholesky QR, twice (Y <-> W)
         char* cur = Yb;
@@ -2215,7 +2335,8 @@ extern "C" pv_status pv_trlanczos_fd(pv_lattice* l, int dtype, double a, double 
         for (int j0 = k; j0 < m; j0 += nbl) {
             const int j1 = j0 + nbl;
             // Wv = p(H~) V_j   (V_j is in S0)
-            if ((st = run_series(l, dtype, nbl, a, b, degree, coef.data(), S0, Wv, Wv, w + Lw.S1, w + Lw.S2, s)) !=
+            if ((st = run_series(l, dtype, nbl, a, b, degree, coef.data(), S0, Wv, Wv, w + Lw.S1, w + Lw.S2, nullptr,
+                                 nullptr, s)) !=
                 PV_OK)
                 return st;
             // full reorthogonalisation against the basis columns < j1, twice;
@@ -3106,7 +3227,9 @@ pv_status tp_forward_keep(pv_lattice* l, int dtype, int nb, double a, double b, 
             st = run_series_keep(l, dtype, nb, a, b, M, coef, psi(i), dst, dst,
                                  [&](int k) { return T.series(i, k); }, s);
         else
-            st = run_series(l, dtype, nb, a, b, M, coef, psi(i), dst, dst, T.wk(1), M >= 2 ? T.wk(2) : T.L0(), s);
+            // w_1 .. w_M have slots of their own, free until the adjoint
+            st = run_series(l, dtype, nb, a, b, M, coef, psi(i), dst, dst, T.wk(1), M >= 2 ? T.wk(2) : T.L0(),
+                            M >= 4 ? T.wk(3) : nullptr, M >= 4 ? T.wk(4) : nullptr, s);
         if (st != PV_OK) return st;
     }
     return PV_OK;

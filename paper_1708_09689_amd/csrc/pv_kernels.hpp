@@ -108,6 +108,7 @@ struct SweepParams {
     const char* cg_src;
     int cg_dim, cg_halo, cg_sidew;   // cg_sidew: some offset has a y and a z step
     int cg_nocompile;   // take a generated kernel only if loaded (else the interpreted one)
+    int real_diag;      // the on-site block's diagonal is real
 };
 
 // Number of workgroups a sweep of an nb-wide block over the lattice uses
@@ -132,6 +133,32 @@ hipError_t codegen_batch_fill_record(const SweepParams& p, int staged, void* dst
 hipError_t launch_batch_codegen(const SweepParams& p, int staged, const void* table, const int* block_inst,
                                 const int* inst_block0, int grid, int red_step, hipStream_t s);
 hipError_t codegen_prepare_batch(const SweepParams& p, int staged);
+
+// Several Chebyshev steps of a 2D lattice in one pass (pv_plane.hip).
+// plane_steps: steps per pass for a run of `steps` steps (series terms, or
+// moment steps with kpm), 0 where the pass does not serve the launch.
+// launch_plane: w_{k+1} .. w_{k+TS} from x = w_k and z = w_{k-1} (NULL: k = 0);
+// y1, y2 receive w_{k+TS-1}, w_{k+TS} (NULL: not stored) and are other buffers
+// than x and z; series: acc_out = acc_in (NULL: eta[0] w_k) + sum over the
+// first `levels` levels of eta[t] w_{k+t}, acc_in may be acc_out; moments:
+// partials [TS][plane_grid][nb][2], reduced by launch_plane_moments.
+struct PlanePass {
+    const void* x;
+    const void* z;
+    void* y1;
+    void* y2;
+    const void* acc_in;
+    void* acc_out;
+    double* partials;
+    double alpha1, alpha;   // of level 1, of the others
+    int levels;
+    const double* eta;      // host, complex [levels + 1]; NULL with partials
+};
+int plane_steps(const SweepParams& p, int steps, bool kpm);
+int plane_grid(const SweepParams& p, int TS);
+hipError_t launch_plane(const SweepParams& p, int TS, const PlanePass& q, hipStream_t s);
+hipError_t launch_plane_moments(const double* partials, int grid, int nb, int n0, int steps, double* mu, int M,
+                                double invD, hipStream_t s);
 
 // Fixed-order reduction of [grid][nb][4] partials.
 //   mode 0: dots[c][0..3] = sums
