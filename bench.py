@@ -483,7 +483,7 @@ def bench_batch(pv, torch, W, dev, n=96, M=1024, nb=16):
     return {"workload": f"{n} TI realisations L~U{{24..96}} ({sites} sites), W~U[0.5,3], nb={nb}, M={M}",
             "batched_c64": {"ms_per_run": round(ms, 2), "GLUP/s": round(lups / (ms * 1e-3) / 1e9, 3),
                             "GB/s": round(b64 / (ms * 1e-3) / 1e9, 1), "first_call_s_incl_capture": round(first, 2),
-                            "mu0_check": ok, "launches_per_run": M // 2 + 1, "graph_replays": batch.stats()[1],
+                            "mu0_check": ok, "sweeps_per_run": M // 2, "graph_replays": batch.stats()[1],
                             "shape": {k: v for k, v in shape.items() if k in ("kernel", "elems_per_lane",
                                                                              "workgroup_size")},
                             "autotune_s": round(tune_s, 2), "autotune_ms_per_step": round(tune_ms, 3)},

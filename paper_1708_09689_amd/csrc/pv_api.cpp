@@ -868,7 +868,7 @@ pv_status spmmv_launch(pv_lattice* l, int dtype, int nb, const void* x, const vo
     } else {
         PV_HIP(pv::launch_sweep(p, num_cus(), s));
     }
-    if (dot_flags) PV_HIP(pv::launch_reduce_dots(p.partials, p.grid, nb, 0, dots, 0, 0, 0.0, s));
+    if (dot_flags) PV_HIP(pv::launch_reduce_dots(p.partials, p.grid, nb, dots, s));
     return PV_OK;
 }
 
@@ -957,9 +957,20 @@ extern "C" pv_status pv_spmmv_noalloc(pv_lattice* l, int dtype, int nb, const vo
 // ---------------------------------------------------------------------------
 namespace {
 
-// Workspace of one sweep per step, the least that pv_kpm_moments takes.
-size_t kpm_sweep_bytes(const pv_lattice* l, int dtype, int nb) {
-    return 2 * partial_bytes(l, nb) + 2 * vec_bytes(l, dtype, nb);
+// Buffers of partial dots with which the moments of many steps are reduced by
+// one launch: 64, within 64 MiB (every step's reduction in the next sweep's
+// first workgroup cost a TI 16^3 step 1.4 of its 5.5 us and a graphene
+// 200 x 150 step of four columns 13 of its 20; a launch per step, 6 us).
+constexpr int kMaxDotBuffers = 64;
+int dot_buffers(size_t bytes, int M) {
+    const size_t fit = std::min<size_t>(kMaxDotBuffers, (size_t(64) << 20) / bytes);
+    return int(std::max<size_t>(2, std::min<size_t>(fit, M / 2)));
+}
+
+// Workspace of one sweep per step; the least that pv_kpm_moments takes has
+// two buffers of partial dots.
+size_t kpm_sweep_bytes(const pv_lattice* l, int dtype, int nb, int buffers) {
+    return buffers * partial_bytes(l, nb) + 2 * vec_bytes(l, dtype, nb);
 }
 
 // Passes of several steps (2D lattices) need two vectors more, since a pass
@@ -969,7 +980,7 @@ size_t plane_dots_bytes(const pv_lattice* l, int dtype, int nb, int ts) {
     return align_up((size_t)kPlaneDots * pv::plane_grid(base_params(l, dtype, nb), ts) * nb * 2 * sizeof(double));
 }
 size_t kpm_plane_bytes(const pv_lattice* l, int dtype, int nb, int ts) {
-    return kpm_sweep_bytes(l, dtype, nb) + 2 * vec_bytes(l, dtype, nb) + plane_dots_bytes(l, dtype, nb, ts);
+    return 4 * vec_bytes(l, dtype, nb) + plane_dots_bytes(l, dtype, nb, ts);
 }
 
 }  // namespace
@@ -977,15 +988,9 @@ size_t kpm_plane_bytes(const pv_lattice* l, int dtype, int nb, int ts) {
 extern "C" size_t pv_kpm_workspace_size(const pv_lattice* l, int dtype, int nb, int M) {
     if (!l || !is_pow2(nb) || nb > PV_MAX_NB || (dtype != PV_C128 && dtype != PV_C64)) return 0;
     const int ts = plane_pass_steps(l, dtype, nb, M / 2, true);
-    return ts ? kpm_plane_bytes(l, dtype, nb, ts) : kpm_sweep_bytes(l, dtype, nb);
+    const size_t sweeps = kpm_sweep_bytes(l, dtype, nb, dot_buffers(partial_bytes(l, nb), M));
+    return ts ? std::max(sweeps, kpm_plane_bytes(l, dtype, nb, ts)) : sweeps;
 }
-
-namespace {
-// Blocks up to this many elements fold each step's moment reduction into the
-// next sweep (one launch per step instead of two; their steps are short
-// enough for launch latency to matter).
-constexpr int64_t kFuseReductionElems = int64_t(1) << 22;
-}  // namespace
 
 namespace {
 
@@ -1005,34 +1010,26 @@ pv_status check_kpm_args(pv_lattice* l, int dtype, int nb, int M, double a, doub
 // for n < M/2, moments from the per-step dots.  wbuf(k) is the buffer that
 // receives w_k (k >= 1); it never aliases w_k's predecessor w_{k-1} (the
 // sweep's x), and it may alias w_{k-2} (the sweep's z, updated in place).
+// part: `buffers` >= 2 buffers of partial_bytes; every `buffers` steps one
+// launch reduces their moments.
 template <class WB, class AFTER>
 pv_status kpm_forward(pv_lattice* l, int dtype, int nb, int M, double a, double b, const void* r, double* mu,
-                      double* part0, double* part1, WB&& wbuf, AFTER&& after, hipStream_t s) {
+                      double* part, int buffers, WB&& wbuf, AFTER&& after, hipStream_t s) {
     pv_status st;
-    double* part[2] = {part0, part1};
+    const int64_t stride = int64_t(partial_bytes(l, nb) / sizeof(double));
     pv::SweepParams p = base_params(l, dtype, nb);
     if ((st = fill_traversal(l, dtype, nb, p)) != PV_OK) return st;
     p.ep = pv::EP_STORE_Y | pv::EP_DOTS;
     const double invD = 1.0 / double(l->n_rows);
-    const bool fuse = l->n_rows * int64_t(nb) <= kFuseReductionElems;
-    // step n's dots go to part[n % 2]; its moments come from the reduction
-    // folded into sweep n + 1, or from a reduction launch of their own
-    int last_grid = 0;
+    int n0 = 0, grid0 = 0;   // first step not reduced yet, rows of its partials
     auto step_sweep = [&](int n) -> hipError_t {
-        p.partials = part[n % 2];
-        p.red_src = nullptr;
-        if (fuse && n > 0) {
-            p.red_src = part[(n - 1) % 2];
-            p.red_out = mu;
-            p.red_grid = last_grid;
-            p.red_mode = n == 1 ? 1 : 2;
-            p.red_M = M;
-            p.red_step = n - 1;
-            p.red_invD = invD;
-        }
-        hipError_t e = pv::launch_sweep(p, num_cus(), s);
-        if (e == hipSuccess && !fuse) e = pv::launch_reduce_dots(p.partials, p.grid, nb, n == 0 ? 1 : 2, mu, M, n, invD, s);
-        last_grid = p.grid;
+        p.partials = part + (n - n0) * stride;
+        if (hipError_t e = pv::launch_sweep(p, num_cus(), s); e != hipSuccess) return e;
+        if (n == n0) grid0 = p.grid;
+        if (p.grid != grid0) return hipErrorInvalidValue;   // one launch shape for all steps
+        if (n + 1 < M / 2 && n + 1 - n0 < buffers) return hipSuccess;
+        const hipError_t e = pv::launch_kpm_reduce(part, stride, grid0, nb, 4, n0, n + 1 - n0, mu, M, invD, s);
+        n0 = n + 1;
         return e;
     };
     // w_1 = H~ w_0
@@ -1058,9 +1055,6 @@ pv_status kpm_forward(pv_lattice* l, int dtype, int nb, int M, double a, double 
         prev = cur;
         cur = next;
     }
-    const int n_last = M / 2 - 1;
-    if (fuse)
-        PV_HIP(pv::launch_reduce_dots(part[n_last % 2], last_grid, nb, n_last == 0 ? 1 : 2, mu, M, n_last, invD, s));
     return PV_OK;
 }
 
@@ -1089,7 +1083,7 @@ pv_status kpm_plane(pv_lattice* l, int dtype, int nb, int M, double a, double b,
         PV_HIP(pv::launch_plane(p, ts, q, s));
         const int done = last ? N : k + ts;
         if (last || done - n0 + ts > kPlaneDots) {
-            PV_HIP(pv::launch_plane_moments(dots, grid, nb, n0, done - n0, mu, M, invD, s));
+            PV_HIP(pv::launch_kpm_reduce(dots, (int64_t)grid * nb * 2, grid, nb, 2, n0, done - n0, mu, M, invD, s));
             n0 = done;
         }
     }
@@ -1102,25 +1096,24 @@ extern "C" pv_status pv_kpm_moments(pv_lattice* l, int dtype, int nb, int M, dou
                                     double* mu, void* work, size_t work_bytes, void* stream) {
     pv_status st;
     if ((st = check_kpm_args(l, dtype, nb, M, a, b, r, mu)) != PV_OK) return st;
-    const size_t need = kpm_sweep_bytes(l, dtype, nb);
+    const size_t need = kpm_sweep_bytes(l, dtype, nb, 2);
     if (!work || work_bytes < need) return fail(PV_ERR_WORKSPACE, "workspace %zu < %zu bytes", work_bytes, need);
     if ((st = ensure_device(l)) != PV_OK) return st;
+    const size_t vb = vec_bytes(l, dtype, nb), pb = partial_bytes(l, nb);
     char* w = static_cast<char*>(work);
-    void* A = w + 2 * partial_bytes(l, nb);
-    void* B = static_cast<char*>(A) + vec_bytes(l, dtype, nb);
+    hipStream_t s = static_cast<hipStream_t>(stream);
     const int ts = plane_pass_steps(l, dtype, nb, M / 2, true);
     if (ts && work_bytes >= kpm_plane_bytes(l, dtype, nb, ts)) {
-        const size_t vb = vec_bytes(l, dtype, nb);
-        char* v = static_cast<char*>(A);
-        void* const W[4] = {v, v + vb, v + 2 * vb, v + 3 * vb};
-        return kpm_plane(l, dtype, nb, M, a, b, ts, r, mu, W, reinterpret_cast<double*>(v + 4 * vb),
-                         static_cast<hipStream_t>(stream));
+        void* const W[4] = {w, w + vb, w + 2 * vb, w + 3 * vb};
+        return kpm_plane(l, dtype, nb, M, a, b, ts, r, mu, W, reinterpret_cast<double*>(w + 4 * vb), s);
     }
-    // w_k in A for odd k, in B for even k (w_{k+1} overwrites w_{k-1})
-    return kpm_forward(l, dtype, nb, M, a, b, r, mu, reinterpret_cast<double*>(w),
-                       reinterpret_cast<double*>(w + partial_bytes(l, nb)),
-                       [&](int k) { return (k & 1) ? A : B; }, [](int, const void*) { return hipSuccess; },
-                       static_cast<hipStream_t>(stream));
+    // w_k in A for odd k, in B for even k (w_{k+1} overwrites w_{k-1}); partial
+    // dots in what is left
+    void* A = w;
+    void* B = w + vb;
+    const int buffers = int(std::min<size_t>(kMaxDotBuffers, (work_bytes - 2 * vb) / pb));
+    return kpm_forward(l, dtype, nb, M, a, b, r, mu, reinterpret_cast<double*>(w + 2 * vb), buffers,
+                       [&](int k) { return (k & 1) ? A : B; }, [](int, const void*) { return hipSuccess; }, s);
 }
 
 extern "C" pv_status pv_kpm_dos(int M, const double* mu, double a, double b, int nE, const double* E, double* rho) {
@@ -1788,7 +1781,7 @@ extern "C" pv_status pv_autotune(pv_lattice* l, int dtype, int nb, const char* c
                 p.ep = pv::EP_STORE_Y | pv::EP_DOTS;
                 p.partials = part;
                 hipError_t e = pv::launch_sweep(p, num_cus(), s);
-                if (e == hipSuccess) e = pv::launch_reduce_dots(part, p.grid, nb, 0, dots, 0, 0, 0.0, s);
+                if (e == hipSuccess) e = pv::launch_reduce_dots(part, p.grid, nb, dots, s);
                 if (e != hipSuccess) return e;
             }
         }
@@ -2502,7 +2495,8 @@ namespace {
 constexpr int kBatchTuneSteps = 8;
 
 struct BatchLayout {
-    size_t tables, block_inst, inst_block0, invD, partials, partial_stride, moments, vecs, total;
+    size_t tables, block_inst, inst_block0, invD, moments, vecs, partials, partial_stride, total;
+    int buffers;   // of partial dots, partial_stride bytes each
     std::vector<size_t> vec_off;  // per instance: A at vec_off[i], B at vec_off[i] + vb_i
     std::vector<int> nblocks;
     int total_blocks;
@@ -2572,6 +2566,7 @@ pv_status batch_counts(const pv_batch* B, int dtype, int nb, int staged, std::ve
 
 // Workspace layout for the direct or the staged kernel; the regions are
 // sized for the larger of the two, so the layout does not depend on which.
+// The buffers of partial dots come last; a smaller workspace holds fewer.
 pv_status batch_layout(const pv_batch* B, int dtype, int nb, int M, int staged, BatchLayout& L) {
     const int n = int(B->lats.size());
     pv_status st;
@@ -2589,10 +2584,6 @@ pv_status batch_layout(const pv_batch* B, int dtype, int nb, int M, int staged, 
     L.block_inst = off; off += align_up(sizeof(int) * cap);
     L.inst_block0 = off; off += align_up(sizeof(int) * (n + 1));
     L.invD = off; off += align_up(sizeof(double) * n);
-    // two partial buffers: step n writes buffer n % 2 while its sweep folds
-    // in the reduction of step n - 1 from the other
-    L.partials = off; off += 2 * align_up((size_t)cap * nb * 4 * sizeof(double));
-    L.partial_stride = align_up((size_t)cap * nb * 4 * sizeof(double));
     L.moments = off; off += align_up((size_t)n * nb * M * sizeof(double));
     L.vecs = off;
     L.vec_off.resize(n);
@@ -2600,7 +2591,10 @@ pv_status batch_layout(const pv_batch* B, int dtype, int nb, int M, int staged, 
         L.vec_off[i] = off;
         off += 2 * vec_bytes(B->lats[i], dtype, nb);
     }
-    L.total = off;
+    L.partials = off;
+    L.partial_stride = align_up((size_t)cap * nb * 4 * sizeof(double));
+    L.buffers = dot_buffers(L.partial_stride, M);
+    L.total = off + L.buffers * L.partial_stride;
     return PV_OK;
 }
 
@@ -2673,7 +2667,9 @@ extern "C" pv_status pv_batch_kpm_moments(pv_batch* B, int dtype, int nb, int M,
         if (reinterpret_cast<uintptr_t>(r[i]) % 16) aligned = 0;
     BatchLayout L;
     if ((st = batch_layout(B, dtype, nb, M, aligned, L)) != PV_OK) return st;
-    if (!work || work_bytes < L.total) return fail(PV_ERR_WORKSPACE, "workspace %zu < %zu bytes", work_bytes, L.total);
+    const size_t need = L.partials + 2 * L.partial_stride;
+    if (!work || work_bytes < need) return fail(PV_ERR_WORKSPACE, "workspace %zu < %zu bytes", work_bytes, need);
+    L.buffers = int(std::min<size_t>(L.buffers, (work_bytes - L.partials) / L.partial_stride));
     for (int i = 0; i < n; ++i)
         if ((st = ensure_device(B->lats[i])) != PV_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -2725,20 +2721,9 @@ extern "C" pv_status pv_batch_kpm_moments(pv_batch* B, int dtype, int nb, int M,
             pv::SweepParams p = batch_params(B, i, dtype, nb);
             p.zero_row = l->d_zero;
             p.slab_rows = slab_rows(l, dtype, nb);
-            // variants 0 and 2 run even steps, 1 and 3 odd ones: dots into
-            // buffer v % 2; every step after the first folds in the previous
-            // step's reduction (this instance's rows of the other buffer)
-            double* part[2] = {reinterpret_cast<double*>(w + L.partials),
-                               reinterpret_cast<double*>(w + L.partials + L.partial_stride)};
-            p.partials = part[v & 1];
-            if (v > 0) {
-                p.red_src = part[(v & 1) ^ 1] + (size_t)inst_block0[i] * nb * 4;
-                p.red_out = reinterpret_cast<double*>(mu_ws) + (size_t)i * nb * M;
-                p.red_grid = L.nblocks[i];
-                p.red_mode = v == 1 ? 1 : 2;
-                p.red_M = M;
-                p.red_invD = invD[i];
-            }
+            // variants 0 and 2 run even steps, 1 and 3 odd ones; dots into the
+            // launch's buffer
+            p.partials = reinterpret_cast<double*>(w + L.partials);
             p.ep = pv::EP_STORE_Y | pv::EP_DOTS;
             p.beta = b[i];
             if (v == 0) {          // w_1 = H~ w_0
@@ -2766,8 +2751,8 @@ extern "C" pv_status pv_batch_kpm_moments(pv_batch* B, int dtype, int nb, int M,
     const int* d_bi = reinterpret_cast<const int*>(w + L.block_inst);
     const int* d_i0 = reinterpret_cast<const int*>(w + L.inst_block0);
     const double* d_invD = reinterpret_cast<const double*>(w + L.invD);
-    const double* d_part[2] = {reinterpret_cast<const double*>(w + L.partials),
-                               reinterpret_cast<const double*>(w + L.partials + L.partial_stride)};
+    const double* d_part = reinterpret_cast<const double*>(w + L.partials);
+    const int64_t stride = int64_t(L.partial_stride / sizeof(double));
     const int vtype = (dtype == PV_C128) ? 0 : B->lats[0]->vtype;
     for (int i = 1; i < n; ++i)
         if (dtype != PV_C128 && B->lats[i]->vtype != vtype && (B->lats[i]->V || B->lats[0]->V))
@@ -2779,17 +2764,18 @@ extern "C" pv_status pv_batch_kpm_moments(pv_batch* B, int dtype, int nb, int M,
     if (p0.cg_src) PV_HIP(pv::codegen_prepare_batch(p0, L.staged));
     PV_HIP(hipStreamBeginCapture(B->cap, hipStreamCaptureModeRelaxed));
     hipError_t e = hipSuccess;
-    // one launch per step (each folds in the previous step's moments), then
-    // the last step's reduction
-    for (int step = 0; step < M / 2 && e == hipSuccess; ++step) {
+    // one launch per step, and one reduction of the moments of every `buffers`
+    // steps
+    for (int step = 0, n0 = 0; step < M / 2 && e == hipSuccess; ++step) {
         const int v = step == 0 ? 0 : (step == 1 ? 1 : (step % 2 == 0 ? 2 : 3));
         e = pv::launch_batch_sweep(p0, L.staged, w + L.tables + (size_t)v * n * rb, d_bi, d_i0, L.total_blocks,
-                                   step - 1, B->cap);
+                                   (step - n0) * stride, B->cap);
+        if (e == hipSuccess && (step + 1 == M / 2 || step + 1 - n0 == L.buffers)) {
+            e = pv::launch_batch_reduce(d_part, stride, d_i0, n, nb, n0, step + 1 - n0,
+                                        reinterpret_cast<double*>(mu_ws), M, d_invD, B->cap);
+            n0 = step + 1;
+        }
     }
-    const int last = M / 2 - 1;
-    if (e == hipSuccess)
-        e = pv::launch_batch_reduce(d_part[last & 1], d_i0, n, nb, last == 0 ? 1 : 2,
-                                    reinterpret_cast<double*>(mu_ws), M, last, d_invD, B->cap);
     hipGraph_t g = nullptr;
     const hipError_t e2 = hipStreamEndCapture(B->cap, &g);
     if (e != hipSuccess || e2 != hipSuccess) {
@@ -3146,7 +3132,15 @@ extern "C" pv_status pv_kpm_moments_ckpt(pv_lattice* l, int dtype, int nb, int M
     auto ck = [&](int j, int which) { return static_cast<void*>(w + vb * (2 * (size_t)j + which)); };
     char* S = w + vb * 2 * (size_t)J;
     void* F[2] = {S + vb * (C + 2), S + vb * (C + 3)};
-    char* part = w + kpm_vjp_core_bytes(l, dtype, nb, M, ckpt);
+    // partial dots of many steps in the two adjoint vectors' place (unused until
+    // the adjoint runs), or of two steps in the buffers after the table
+    const size_t pb = partial_bytes(l, nb);
+    int buffers = int(std::min<size_t>(kMaxDotBuffers, 2 * vb / pb));
+    char* part = S + vb * (size_t)C;
+    if (buffers < 2) {
+        buffers = 2;
+        part = w + kpm_vjp_core_bytes(l, dtype, nb, M, ckpt);
+    }
     PV_HIP(pv::launch_copy(r, ck(0, 0), vbytes, s));
     // w_k goes straight to its checkpoint slot (jC + rem, rem in {0, 1});
     // with one segment (C >= M/2) w_2..w_N go to the segment slots, where
@@ -3162,8 +3156,7 @@ extern "C" pv_status pv_kpm_moments_ckpt(pv_lattice* l, int dtype, int nb, int M
         if (C == 1 && k - 1 < J) return pv::launch_copy(y, ck(k - 1, 1), vbytes, s);
         return hipSuccess;
     };
-    return kpm_forward(l, dtype, nb, M, a, b, r, mu, reinterpret_cast<double*>(part),
-                       reinterpret_cast<double*>(part + partial_bytes(l, nb)), wbuf, after, s);
+    return kpm_forward(l, dtype, nb, M, a, b, r, mu, reinterpret_cast<double*>(part), buffers, wbuf, after, s);
 }
 
 extern "C" pv_status pv_kpm_moments_vjp_ckpt(pv_lattice* l, int dtype, int nb, int M, double a, double b,

@@ -451,14 +451,14 @@ hipError_t codegen_prepare_batch(const SweepParams& p, int staged) {
 }
 
 hipError_t launch_batch_codegen(const SweepParams& p, int staged, const void* table, const int* block_inst,
-                                const int* inst_block0, int grid, int red_step, hipStream_t s) {
+                                const int* inst_block0, int grid, int64_t part_off, hipStream_t s) {
     g_err.clear();
     if (staged && p.ep != (EP_STORE_Y | EP_DOTS)) return hipErrorInvalidValue;
     Compiled c;
     int nt = 0;
     size_t lds = 0;
     if (const hipError_t e = batch_function(p, staged, false, c, nt, lds); e != hipSuccess) return e;
-    void* args[] = {&table, &block_inst, &inst_block0, &red_step};
+    void* args[] = {&table, &block_inst, &inst_block0, &part_off};
     return hipModuleLaunchKernel(c.fn, unsigned(grid), 1, 1, unsigned(nt), 1, 1, unsigned(lds), s, args, nullptr);
 }
 

@@ -23,13 +23,13 @@ hipError_t batch_fill_record_generic(const SweepParams& p, int staged, void* dst
 }
 
 hipError_t launch_batch_sweep_generic(const SweepParams& p, int staged, const void* table, const int* block_inst,
-                                      const int* inst_block0, int grid, int red_step, hipStream_t s) {
+                                      const int* inst_block0, int grid, int64_t part_off, hipStream_t s) {
     switch (p.n_orb) {
-        case 1: return launch_batch_sweep_fam<PatGeneric<1>>(p, staged, table, block_inst, inst_block0, grid, red_step,
+        case 1: return launch_batch_sweep_fam<PatGeneric<1>>(p, staged, table, block_inst, inst_block0, grid, part_off,
                                                              s);
-        case 2: return launch_batch_sweep_fam<PatGeneric<2>>(p, staged, table, block_inst, inst_block0, grid, red_step,
+        case 2: return launch_batch_sweep_fam<PatGeneric<2>>(p, staged, table, block_inst, inst_block0, grid, part_off,
                                                              s);
-        case 4: return launch_batch_sweep_fam<PatGeneric<4>>(p, staged, table, block_inst, inst_block0, grid, red_step,
+        case 4: return launch_batch_sweep_fam<PatGeneric<4>>(p, staged, table, block_inst, inst_block0, grid, part_off,
                                                              s);
         default: return hipErrorInvalidValue;
     }

@@ -12,8 +12,8 @@ hipError_t batch_fill_record_weyl(const SweepParams& p, int staged, void* dst, i
 }
 
 hipError_t launch_batch_sweep_weyl(const SweepParams& p, int staged, const void* table, const int* block_inst,
-                                  const int* inst_block0, int grid, int red_step, hipStream_t s) {
-    return launch_batch_sweep_fam<PatWeyl>(p, staged, table, block_inst, inst_block0, grid, red_step, s);
+                                  const int* inst_block0, int grid, int64_t part_off, hipStream_t s) {
+    return launch_batch_sweep_fam<PatWeyl>(p, staged, table, block_inst, inst_block0, grid, part_off, s);
 }
 
 }  // namespace pv

@@ -9,25 +9,73 @@ namespace {
 
 // ------------------------------------------------------------------ reductions
 
-// One wave per block column: the fixed-order reduction shared with the
-// reduction folded into a sweep.
-__global__ __launch_bounds__(64) void reduce_dots_kernel(const double* __restrict__ partials, int grid, int nb,
-                                                         int mode, double* out, int M, int step, double inv_D) {
-    reduce_column_wave(partials, grid, nb, blockIdx.x, mode, out, M, step, inv_D, threadIdx.x);
+// Sums over the `grid` rows of partials, `pitch` doubles apart, of the first N
+// doubles of a row, in a fixed order: lane-strided, an xor tree per wave, then
+// the four waves (the result is complete in thread 0).
+template <int N>
+__device__ __forceinline__ void reduce_rows(const double* __restrict__ q, int grid, int pitch, double (&s)[N]) {
+    __shared__ double part[kBlock / 64][N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) s[k] = 0.0;
+#pragma unroll 4
+    for (int b = threadIdx.x; b < grid; b += kBlock) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) s[k] += q[(size_t)b * pitch + k];
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        for (int m = 32; m >= 1; m >>= 1) s[k] += __shfl_xor(s[k], m);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][k] = s[k];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            for (int w = 1; w < kBlock / 64; ++w) s[k] += part[w][k];
+    }
+    __syncthreads();
 }
 
-// Per-instance fixed-order reduction of a batched sweep: one wave per
-// (instance i, column c) sums the partials of the instance's workgroups
-// [inst_block0[i], inst_block0[i+1]) and updates mu[i][c][.] (modes 1, 2 of
-// reduce_dots_kernel), in the order of the reduction folded into a sweep.
-__global__ __launch_bounds__(64) void batch_reduce_kernel(const double* __restrict__ partials,
-                                                          const int* __restrict__ inst_block0, int nb, int mode,
-                                                          double* mu, int M, int step,
-                                                          const double* __restrict__ invD) {
+// One workgroup per block column.  (At 2048 rows and 8 columns: 6.4 us as one
+// wave per column.)
+__global__ __launch_bounds__(kBlock) void reduce_dots_kernel(const double* __restrict__ partials, int grid, int nb,
+                                                             double* __restrict__ dots) {
+    double s[4];
+    reduce_rows(partials + (size_t)blockIdx.x * 4, grid, nb * 4, s);
+    if (threadIdx.x == 0)
+        for (int k = 0; k < 4; ++k) dots[blockIdx.x * 4 + k] = s[k];
+}
+
+// Moments of step n = n0 + step, column c (launch_kpm_reduce); the steps after
+// the first need mu_0 and mu_1, which with n0 = 0 every workgroup sums for
+// itself from step 0's partials.
+__device__ __forceinline__ void kpm_reduce(const double* __restrict__ partials, int64_t stride, int grid, int nb,
+                                           int width, int c, int n0, int step, double* __restrict__ mu, double invD) {
+    const int n = n0 + step;
+    double s[2], m[2];
+    reduce_rows(partials + step * stride + c * width, grid, nb * width, s);
+    if (n0 == 0 && n > 0) reduce_rows(partials + c * width, grid, nb * width, m);
+    if (threadIdx.x == 0) {
+        for (int k = 0; k < 2; ++k)
+            mu[2 * n + k] = n == 0 ? s[k] * invD : 2.0 * s[k] * invD - (n0 == 0 ? m[k] * invD : mu[k]);
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void kpm_reduce_kernel(const double* __restrict__ partials, int64_t stride,
+                                                            int grid, int nb, int width, int n0,
+                                                            double* __restrict__ mu, int M, double invD) {
+    kpm_reduce(partials, stride, grid, nb, width, blockIdx.y, n0, blockIdx.x, mu + (size_t)blockIdx.y * M, invD);
+}
+
+// The same for every instance of a batch: instance and column in blockIdx.x.
+__global__ __launch_bounds__(kBlock) void batch_reduce_kernel(const double* __restrict__ partials, int64_t stride,
+                                                              const int* __restrict__ inst_block0, int nb, int n0,
+                                                              double* __restrict__ mu, int M,
+                                                              const double* __restrict__ invD) {
     const int i = blockIdx.x / nb, c = blockIdx.x % nb;
     const int b0 = inst_block0[i], b1 = inst_block0[i + 1];
-    reduce_column_wave(partials + (size_t)b0 * nb * 4, b1 - b0, nb, c, mode, mu + (size_t)i * nb * M, M, step,
-                       invD[i], threadIdx.x);
+    kpm_reduce(partials + (size_t)b0 * nb * 4, stride, b1 - b0, nb, 4, c, n0, blockIdx.y, mu + (size_t)blockIdx.x * M,
+               invD[i]);
 }
 
 template <typename T>
@@ -281,10 +329,15 @@ hipError_t launch_sweep(SweepParams& p, int num_cus, hipStream_t s) {
     }
 }
 
-hipError_t launch_reduce_dots(const double* partials, int grid, int nb, int mode, double* out, int M,
-                              int step, double inv_D, hipStream_t s) {
-    hipLaunchKernelGGL(reduce_dots_kernel, dim3(nb), dim3(64), 0, s, partials, grid, nb, mode, out, M, step,
-                       inv_D);
+hipError_t launch_reduce_dots(const double* partials, int grid, int nb, double* dots, hipStream_t s) {
+    hipLaunchKernelGGL(reduce_dots_kernel, dim3(nb), dim3(kBlock), 0, s, partials, grid, nb, dots);
+    return hipGetLastError();
+}
+
+hipError_t launch_kpm_reduce(const double* partials, int64_t stride, int grid, int nb, int width, int n0, int steps,
+                             double* mu, int M, double invD, hipStream_t s) {
+    hipLaunchKernelGGL(kpm_reduce_kernel, dim3(steps, nb), dim3(kBlock), 0, s, partials, stride, grid, nb, width, n0,
+                       mu, M, invD);
     return hipGetLastError();
 }
 
@@ -364,25 +417,25 @@ hipError_t batch_fill_record(const SweepParams& p, int staged, void* dst, int* n
 }
 
 hipError_t launch_batch_sweep(const SweepParams& p, int staged, const void* table, const int* block_inst,
-                              const int* inst_block0, int grid, int red_step, hipStream_t s) {
+                              const int* inst_block0, int grid, int64_t part_off, hipStream_t s) {
     const void* t = table;
     const int* bi = block_inst;
     const int* i0 = inst_block0;
     switch (p.family) {
-        case FAM_TI: return launch_batch_sweep_ti(p, staged, t, bi, i0, grid, red_step, s);
-        case FAM_GRAPHENE2: return launch_batch_sweep_graphene2(p, staged, t, bi, i0, grid, red_step, s);
-        case FAM_GRAPHENE4: return launch_batch_sweep_graphene4(p, staged, t, bi, i0, grid, red_step, s);
-        case FAM_WEYL: return launch_batch_sweep_weyl(p, staged, t, bi, i0, grid, red_step, s);
+        case FAM_TI: return launch_batch_sweep_ti(p, staged, t, bi, i0, grid, part_off, s);
+        case FAM_GRAPHENE2: return launch_batch_sweep_graphene2(p, staged, t, bi, i0, grid, part_off, s);
+        case FAM_GRAPHENE4: return launch_batch_sweep_graphene4(p, staged, t, bi, i0, grid, part_off, s);
+        case FAM_WEYL: return launch_batch_sweep_weyl(p, staged, t, bi, i0, grid, part_off, s);
         default:
-            return p.cg_src ? launch_batch_codegen(p, staged, t, bi, i0, grid, red_step, s)
-                            : launch_batch_sweep_generic(p, staged, t, bi, i0, grid, red_step, s);
+            return p.cg_src ? launch_batch_codegen(p, staged, t, bi, i0, grid, part_off, s)
+                            : launch_batch_sweep_generic(p, staged, t, bi, i0, grid, part_off, s);
     }
 }
 
-hipError_t launch_batch_reduce(const double* partials, const int* inst_block0, int n_inst, int nb, int mode,
-                               double* mu, int M, int step, const double* invD, hipStream_t s) {
-    hipLaunchKernelGGL(batch_reduce_kernel, dim3(n_inst * nb), dim3(64), 0, s, partials, inst_block0, nb, mode, mu,
-                       M, step, invD);
+hipError_t launch_batch_reduce(const double* partials, int64_t stride, const int* inst_block0, int n_inst, int nb,
+                               int n0, int steps, double* mu, int M, const double* invD, hipStream_t s) {
+    hipLaunchKernelGGL(batch_reduce_kernel, dim3(n_inst * nb, steps), dim3(kBlock), 0, s, partials, stride,
+                       inst_block0, nb, n0, mu, M, invD);
     return hipGetLastError();
 }
 

@@ -95,13 +95,6 @@ struct SweepParams {
     unsigned ep;
     double* partials;     // [grid][nb][4] when EP_DOTS
     int grid;             // set by launch_sweep: number of workgroups
-    // reduction of the previous sweep's partials (red_grid rows) into
-    // red_out, by the first wave of workgroup 0 before its tiles (modes of
-    // launch_reduce_dots); NULL red_src: none
-    const double* red_src;
-    double* red_out;
-    int red_grid, red_mode, red_M, red_step;
-    double red_invD;
     // generated kernels (generic stencils): source of the stencil's pattern
     // struct pv::PatCG, NULL for the interpreted generic kernels; its
     // lattice dimension and side-row flags (x halo, rows at w -+ 1)
@@ -131,7 +124,7 @@ int codegen_instances();
 // instance ahead of a graph capture.
 hipError_t codegen_batch_fill_record(const SweepParams& p, int staged, void* dst, int* nblocks);
 hipError_t launch_batch_codegen(const SweepParams& p, int staged, const void* table, const int* block_inst,
-                                const int* inst_block0, int grid, int red_step, hipStream_t s);
+                                const int* inst_block0, int grid, int64_t part_off, hipStream_t s);
 hipError_t codegen_prepare_batch(const SweepParams& p, int staged);
 
 // Several Chebyshev steps of a 2D lattice in one pass (pv_plane.hip).
@@ -141,7 +134,7 @@ hipError_t codegen_prepare_batch(const SweepParams& p, int staged);
 // y1, y2 receive w_{k+TS-1}, w_{k+TS} (NULL: not stored) and are other buffers
 // than x and z; series: acc_out = acc_in (NULL: eta[0] w_k) + sum over the
 // first `levels` levels of eta[t] w_{k+t}, acc_in may be acc_out; moments:
-// partials [TS][plane_grid][nb][2], reduced by launch_plane_moments.
+// partials [TS][plane_grid][nb][2] (launch_kpm_reduce with width 2).
 struct PlanePass {
     const void* x;
     const void* z;
@@ -157,15 +150,16 @@ struct PlanePass {
 int plane_steps(const SweepParams& p, int steps, bool kpm);
 int plane_grid(const SweepParams& p, int TS);
 hipError_t launch_plane(const SweepParams& p, int TS, const PlanePass& q, hipStream_t s);
-hipError_t launch_plane_moments(const double* partials, int grid, int nb, int n0, int steps, double* mu, int M,
-                                double invD, hipStream_t s);
 
-// Fixed-order reduction of [grid][nb][4] partials.
-//   mode 0: dots[c][0..3] = sums
-//   mode 1: KPM first step: mu[c][0] = xx/D, mu[c][1] = Re xy / D
-//   mode 2: KPM step n >= 1: mu[c][2n] = 2 xx/D - mu[c][0], mu[c][2n+1] = 2 Re xy/D - mu[c][1]
-hipError_t launch_reduce_dots(const double* partials, int grid, int nb, int mode, double* out,
-                              int M, int step, double inv_D, hipStream_t s);
+// Fixed-order sums of [grid][nb][4] partials: dots[c][0..3].
+hipError_t launch_reduce_dots(const double* partials, int grid, int nb, double* dots, hipStream_t s);
+// Moments of the KPM steps n0 .. n0 + steps - 1 from their sweeps' partials,
+// step s at partials + s * stride, [grid][nb][width] (width 4 or 2: <w,w> and
+// Re <w,w'> come first), summed in a fixed order:
+//   n = 0: mu[c][0] = xx / D, mu[c][1] = xy / D
+//   else:  mu[c][2n] = 2 xx / D - mu[c][0], mu[c][2n+1] = 2 xy / D - mu[c][1]
+hipError_t launch_kpm_reduce(const double* partials, int64_t stride, int grid, int nb, int width, int n0, int steps,
+                             double* mu, int M, double invD, hipStream_t s);
 
 hipError_t launch_scale_block(int dtype, int64_t n_elem, const void* x, double re, double im,
                               void* y, hipStream_t s);
@@ -225,12 +219,13 @@ size_t batch_record_bytes();
 // dst = 0 (bytes a multiple of 4)
 hipError_t launch_zero(void* dst, size_t bytes, hipStream_t s);
 hipError_t batch_fill_record(const SweepParams& p, int staged, void* dst, int* nblocks);
-// red_step: the moment step the records' folded reductions write (their
-// red_* fields say what to reduce; see SweepParams)
+// part_off: doubles from the records' partials to those of this step
 hipError_t launch_batch_sweep(const SweepParams& p, int staged, const void* table, const int* block_inst,
-                              const int* inst_block0, int grid, int red_step, hipStream_t s);
-hipError_t launch_batch_reduce(const double* partials, const int* inst_block0, int n_inst, int nb, int mode,
-                               double* mu, int M, int step, const double* invD, hipStream_t s);
+                              const int* inst_block0, int grid, int64_t part_off, hipStream_t s);
+// launch_kpm_reduce of every instance: its rows of a step's partials are
+// [inst_block0[i], inst_block0[i + 1]), its moments mu[i].
+hipError_t launch_batch_reduce(const double* partials, int64_t stride, const int* inst_block0, int n_inst, int nb,
+                               int n0, int steps, double* mu, int M, const double* invD, hipStream_t s);
 
 #endif  // PV_RTC
 }  // namespace pv

@@ -386,41 +386,6 @@ void plane_kernel(PlaneArgs<T, VT> a) {
     }
 }
 
-// Moments mu_{2n}, mu_{2n+1} of steps n = n0, n0 + 1, ... from their passes'
-// partials [step][grid][nb][2]: one wave per step and column, fixed order.
-// Step 0 gives mu_0 and mu_1, the others twice their dots over D less those
-// two, which with n0 = 0 every wave sums for itself from step 0's partials.
-__global__ __launch_bounds__(64) void plane_moments_kernel(const double* __restrict__ partials, int grid, int nb, int n0,
-                                                           double* __restrict__ mu, int M, double invD) {
-    const int n = n0 + blockIdx.x, c = blockIdx.y, lane = threadIdx.x;
-    auto sum = [&](int step, double& s0, double& s1) {
-        const double* q = partials + ((size_t)step * grid * nb + c) * 2;
-        s0 = s1 = 0.0;
-        for (int b = lane; b < grid; b += 64) {
-            s0 += q[(size_t)b * nb * 2];
-            s1 += q[(size_t)b * nb * 2 + 1];
-        }
-        for (int m = 32; m >= 1; m >>= 1) {
-            s0 += __shfl_xor(s0, m);
-            s1 += __shfl_xor(s1, m);
-        }
-    };
-    double s0, s1, m0 = 0.0, m1 = 0.0;
-    sum(blockIdx.x, s0, s1);
-    if (n0 == 0) {
-        sum(0, m0, m1);
-        m0 *= invD;
-        m1 *= invD;
-    } else if (lane == 0) {
-        m0 = mu[(size_t)c * M];
-        m1 = mu[(size_t)c * M + 1];
-    }
-    if (lane == 0) {
-        mu[(size_t)c * M + 2 * n] = n == 0 ? m0 : 2.0 * s0 * invD - m0;
-        mu[(size_t)c * M + 2 * n + 1] = n == 0 ? m1 : 2.0 * s1 * invD - m1;
-    }
-}
-
 int log2_of(int v) {
     int l = 0;
     while ((1 << l) < v) ++l;
@@ -547,12 +512,6 @@ hipError_t launch_plane(const SweepParams& p, int TS, const PlanePass& q, hipStr
         }
         return hipErrorInvalidValue;
     });
-}
-
-hipError_t launch_plane_moments(const double* partials, int grid, int nb, int n0, int steps, double* mu, int M,
-                                double invD, hipStream_t s) {
-    hipLaunchKernelGGL(plane_moments_kernel, dim3(steps, nb), dim3(64), 0, s, partials, grid, nb, n0, mu, M, invD);
-    return hipGetLastError();
 }
 
 }  // namespace pv

@@ -113,10 +113,6 @@ struct KArgs {
     const int* offs;
     const double* colp;
     double* partials;
-    const double* red_src;   // previous sweep's partials reduced at the start (or NULL)
-    double* red_out;
-    int red_grid, red_mode, red_M, red_step;
-    double red_invD;
     int64_t n_elem, ntiles;
     int tpb;
     // traversal: XCD part k (rows y in [Ly k/8, Ly (k+1)/8), all z) is swept
@@ -400,64 +396,14 @@ __device__ __forceinline__ void slot_coefficients(const double* coef, int o, int
 // The work of one workgroup: tiles [t0, t1) of the part of the lattice made of
 // rows y in [y0, y0 + ny) (all z), swept slab by slab; partial dots go to
 // partials[b_out].
-// Fixed-order sum over the partial rows of block column c by one wave
-// (lane-strided sums, then an xor tree); lane 0 stores the result: mode 0
-// the four dots, mode 1 mu_0 and mu_1 (divided by D), mode 2 the moments
-// mu_2step = 2 xx / D - mu_0 and mu_2step+1 = 2 xy / D - mu_1.
-__device__ __forceinline__ void reduce_column_wave(const double* __restrict__ partials, int grid, int nb, int c,
-                                                  int mode, double* out, int M, int step, double inv_D, int lane) {
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    for (int b = lane; b < grid; b += 64) {
-        const double* q = partials + ((size_t)b * nb + c) * 4;
-        s0 += q[0];
-        s1 += q[1];
-        s2 += q[2];
-        s3 += q[3];
-    }
-    for (int m = 32; m >= 1; m >>= 1) {
-        s0 += __shfl_xor(s0, m);
-        s1 += __shfl_xor(s1, m);
-        s2 += __shfl_xor(s2, m);
-        s3 += __shfl_xor(s3, m);
-    }
-    if (lane == 0) {
-        if (mode == 0) {
-            out[c * 4 + 0] = s0;
-            out[c * 4 + 1] = s1;
-            out[c * 4 + 2] = s2;
-            out[c * 4 + 3] = s3;
-        } else if (mode == 1) {
-            out[(size_t)c * M + 0] = s0 * inv_D;
-            out[(size_t)c * M + 1] = s1 * inv_D;
-        } else {
-            double* mu = out + (size_t)c * M;
-            mu[2 * step] = 2.0 * s0 * inv_D - mu[0];
-            mu[2 * step + 1] = 2.0 * s1 * inv_D - mu[1];
-        }
-    }
-}
-
-// The previous sweep's reduction, folded into this one: the first wave of
-// the leading workgroup (workgroup 0, or an instance's first in a batched
-// launch) reduces every column before its tiles.  The partials were written
-// by the previous launch, so they are complete and visible.
-template <typename T, typename VT>
-__device__ __forceinline__ void fused_reduction(const KArgs<T, VT>& a, bool lead, int tid) {
-    if (a.red_src != nullptr && lead && tid < 64)
-        for (int c = 0; c < a.nb; ++c)
-            reduce_column_wave(a.red_src, a.red_grid, a.nb, c, a.red_mode, a.red_out, a.red_M, a.red_step,
-                               a.red_invD, tid);
-}
-
 template <class P, typename T, typename VT>
 __device__ __forceinline__ void sweep_block(const KArgs<T, VT>& a, int b_out, int y0, int ny, int64_t t0,
-                                            int64_t t1, bool lead) {
+                                            int64_t t1) {
     constexpr int NO = P::NO;
     const int tid = threadIdx.x;
     const int nb = a.nb;
     const int c = tid & (nb - 1);
     const int o = (tid >> a.lognb) & (NO - 1);
-    fused_reduction(a, lead, tid);
 
     double al = a.alpha, be = a.beta, ga = a.gamma;
     if (a.colp != nullptr) {
@@ -639,27 +585,27 @@ void sweep_kernel(KArgs<T, VT> a) {
     const int64_t ntl = (int64_t)a.ntx * ny * a.Lz;
     const int64_t t0 = (int64_t)(b >> 3) * a.tpb;
     const int64_t t1 = min(t0 + a.tpb, ntl);
-    sweep_block<P, T, VT>(a, b, y0, ny, t0, t1, b == 0);
+    sweep_block<P, T, VT>(a, b, y0, ny, t0, t1);
 }
 
 // One sweep over a batch of independent lattices of the same family in a
 // single launch: workgroup b serves instance block_inst[b], whose argument
 // record (geometry, buffers, scale and shift) is table[instance]; each
 // instance's workgroups are consecutive and cover its tiles in order.
-// red_step: the step whose moments the records' folded reduction writes.
+// part_off: doubles from the records' partials to this step's.
 template <class P, typename T, typename VT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(PV_SWEEP_WAVES_PER_EU)))
 void batch_sweep_kernel(const KArgs<T, VT>* __restrict__ table, const int* __restrict__ block_inst,
-                        const int* __restrict__ inst_block0, int red_step) {
+                        const int* __restrict__ inst_block0, int64_t part_off) {
     const int b = blockIdx.x;
     const int i = __builtin_amdgcn_readfirstlane(block_inst[b]);
     const int lb = b - __builtin_amdgcn_readfirstlane(inst_block0[i]);
     KArgs<T, VT> a = table[i];
-    a.red_step = red_step;
+    a.partials += part_off;
     const int64_t ntl = (int64_t)a.ntx * a.Ly * a.Lz;
     const int64_t t0 = (int64_t)lb * a.tpb;
     const int64_t t1 = min(t0 + a.tpb, ntl);
-    sweep_block<P, T, VT>(a, b, 0, a.Ly, t0, t1, lb == 0);
+    sweep_block<P, T, VT>(a, b, 0, a.Ly, t0, t1);
 }
 
 // ---------------------------------------------------------------------------
@@ -956,7 +902,6 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
     const int c = tid & (nb - 1);
     const int o = (tid >> a.lognb) & (NO - 1);
     const int site = a.st_site;
-    fused_reduction(a, part == 0 && jb == 0, tid);
 
     // per-column alpha, beta, gamma only in the run-time epilogue (the
     // specialised ones are launched with uniform values)
@@ -1192,13 +1137,13 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
 template <class P, typename T, typename VT, int E, unsigned EPM, int NT = kBlock>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(PV_STAGED_WAVES_PER_EU)))
 void batch_staged_kernel(const KArgs<T, VT>* __restrict__ table, const int* __restrict__ block_inst,
-                         const int* __restrict__ inst_block0, int red_step) {
+                         const int* __restrict__ inst_block0, int64_t part_off) {
     const int b = blockIdx.x;
     const int i = __builtin_amdgcn_readfirstlane(block_inst[b]);
     const int b0 = __builtin_amdgcn_readfirstlane(inst_block0[i]);
     const int b1 = __builtin_amdgcn_readfirstlane(inst_block0[i + 1]);
     KArgs<T, VT> a = table[i];
-    a.red_step = red_step;
+    a.partials += part_off;
     const int lb = b - b0;
     staged_block<P, T, VT, E, EPM, NT>(a, b, lb & 7, lb >> 3, (b1 - b0) >> 3);
 }
@@ -1268,13 +1213,6 @@ void make_kargs(const SweepParams& p, bool whole_part, KArgs<T, VT>& a) {
     a.offs = p.offs;
     a.colp = p.colp;
     a.partials = p.partials;
-    a.red_src = p.red_src;
-    a.red_out = p.red_out;
-    a.red_grid = p.red_grid;
-    a.red_mode = p.red_mode;
-    a.red_M = p.red_M;
-    a.red_step = p.red_step;
-    a.red_invD = p.red_invD;
     a.Lx = int(p.L[0]);
     a.Ly = int(p.L[1]);
     a.Lz = int(p.L[2]);
@@ -1568,7 +1506,7 @@ hipError_t batch_fill_record_fam(const SweepParams& p, int staged, void* dst, in
 // One step of a batched sweep: every instance's workgroups in one launch.
 template <class P>
 hipError_t launch_batch_sweep_fam(const SweepParams& p, int staged, const void* table, const int* block_inst,
-                                  const int* inst_block0, int grid, int red_step, hipStream_t s) {
+                                  const int* inst_block0, int grid, int64_t part_off, hipStream_t s) {
     return dispatch_types(p.dtype, p.vtype, [&](auto tt, auto tv) -> hipError_t {
         using T = typename decltype(tt)::type;
         using VT = typename decltype(tv)::type;
@@ -1586,7 +1524,7 @@ hipError_t launch_batch_sweep_fam(const SweepParams& p, int staged, const void* 
                         if (e != hipSuccess) return e;
                     }
                     hipLaunchKernelGGL((batch_staged_kernel<P, T, VT, E, KPM, NT>), dim3(grid), dim3(NT), lds, s,
-                                       static_cast<const KArgs<T, VT>*>(table), block_inst, inst_block0, red_step);
+                                       static_cast<const KArgs<T, VT>*>(table), block_inst, inst_block0, part_off);
                     return hipGetLastError();
                 };
                 if (p.ep != KPM) return hipErrorInvalidValue;
@@ -1606,7 +1544,7 @@ hipError_t launch_batch_sweep_fam(const SweepParams& p, int staged, const void* 
             }
         }
         hipLaunchKernelGGL((batch_sweep_kernel<P, T, VT>), dim3(grid), dim3(kBlock), 0, s,
-                           static_cast<const KArgs<T, VT>*>(table), block_inst, inst_block0, red_step);
+                           static_cast<const KArgs<T, VT>*>(table), block_inst, inst_block0, part_off);
         return hipGetLastError();
     });
 }
@@ -1620,7 +1558,7 @@ hipError_t launch_batch_sweep_fam(const SweepParams& p, int staged, const void* 
     hipError_t launch_sweep_##name(SweepParams& p, int num_cus, hipStream_t s);                              \
     hipError_t batch_fill_record_##name(const SweepParams& p, int staged, void* dst, int* nblocks);          \
     hipError_t launch_batch_sweep_##name(const SweepParams& p, int staged, const void* table,                \
-                                         const int* block_inst, const int* inst_block0, int grid, int red_step, \
+                                         const int* block_inst, const int* inst_block0, int grid, int64_t part_off, \
                                          hipStream_t s);
 PV_FAMILY_ENTRY_POINTS(ti)
 PV_FAMILY_ENTRY_POINTS(graphene2)
