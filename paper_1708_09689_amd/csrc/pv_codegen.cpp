@@ -243,24 +243,33 @@ const char* tname() {
     return sizeof(T) == 8 ? "double" : "float";
 }
 
-// Staged sweep of E elements per lane, NT lanes, epilogue flags epm (0: read
-// at run time): the set-up of launch_staged with the generated kernel.
-template <class P, typename T, typename VT, int E, int NT>
-hipError_t staged_go(SweepParams& p, int num_cus, hipStream_t s, unsigned epm) {
+// Staged sweep of E complex numbers per lane, NT lanes, epilogue flags epm (0:
+// read at run time), elements of W columns: the set-up of launch_staged_w with
+// the generated kernel.
+template <class P, typename T, typename VT, int E, int NT, int W>
+hipError_t staged_go_w(SweepParams& p, int num_cus, hipStream_t s, unsigned epm) {
     KArgs<T, VT> a;
     make_kargs<P, T, VT>(p, false, a);
-    const size_t lds = staged_lds_bytes_for<P, T, E, NT>(epm == 0u || (epm & EP_ACC_ADD) != 0u);
+    const size_t lds = staged_lds_bytes_for<P, T, E, NT, W>(epm == 0u || (epm & EP_ACC_ADD) != 0u);
     char expr[160];
-    std::snprintf(expr, sizeof expr, "&pv::staged_kernel<pv::PatCG, %s, %s, %d, %uu, %d>", tname<T>(), tname<VT>(),
-                  E, epm, NT);
+    std::snprintf(expr, sizeof expr, "&pv::staged_kernel<pv::PatCG, %s, %s, %d, %uu, %d, %d>", tname<T>(), tname<VT>(),
+                  E, epm, NT, W);
     Compiled c;
     if (const hipError_t e = function_for(p.cg_src, expr, NT, lds, p.cg_nocompile != 0, c); e != hipSuccess) return e;
     int G8 = p.st_G8 > 0 ? p.st_G8 : (num_cus >= 8 ? num_cus / 8 : 1) * c.occ;
     if (G8 > 256) G8 = 256;
-    G8 = staged_setup<P, T, VT, E, NT>(p, G8, false, a);
+    G8 = staged_setup<P, T, VT, E, NT, W>(p, G8, false, a);
     p.grid = 8 * G8;
     void* args[] = {&a};
     return hipModuleLaunchKernel(c.fn, unsigned(p.grid), 1, 1, NT, 1, 1, unsigned(lds), s, args, nullptr);
+}
+
+template <class P, typename T, typename VT, int E, int NT>
+hipError_t staged_go(SweepParams& p, int num_cus, hipStream_t s, unsigned epm) {
+    if constexpr (sizeof(T) == 4) {
+        if (epm != 0u && paired<T>(p)) return staged_go_w<P, T, VT, E, NT, 2>(p, num_cus, s, epm);
+    }
+    return staged_go_w<P, T, VT, E, NT, 1>(p, num_cus, s, epm);
 }
 
 // Epilogue specialisations as for the built-in families: the Chebyshev step
@@ -274,8 +283,8 @@ hipError_t staged_ep(SweepParams& p, int num_cus, hipStream_t s) {
     if constexpr (E != E0) {
         // a tile whose rows (six side rows with SIDE_W) overflow the CU's LDS
         // takes the shortest tile instead
-        if (staged_lds_bytes_for<P, T, E, kBlock>(true) > max_lds() ||
-            (p.st_nt == 512 && staged_lds_bytes_for<P, T, E, 512>(true) > max_lds()))
+        if (staged_lds_bytes_for<P, T, E, kBlock, 1>(true) > max_lds() ||
+            (p.st_nt == 512 && staged_lds_bytes_for<P, T, E, 512, 1>(true) > max_lds()))
             return staged_ep<P, T, VT, E0>(p, num_cus, s);
     }
     if (p.colp == nullptr) {
@@ -284,7 +293,7 @@ hipError_t staged_ep(SweepParams& p, int num_cus, hipStream_t s) {
         else if (p.ep == SERIES) epm = SERIES;
         else if (p.ep == PLAIN) epm = p.gamma == 0.0 ? (PLAIN | EP_NO_Z) : PLAIN;
         if (epm != 0u) {
-            if (p.st_nt == 512 && staged_lds_bytes_for<P, T, E, 512>(true) <= max_lds())
+            if (p.st_nt == 512 && staged_lds_bytes_for<P, T, E, 512, 1>(true) <= max_lds())
                 return staged_go<P, T, VT, E, 512>(p, num_cus, s, epm);
             return staged_go<P, T, VT, E, kBlock>(p, num_cus, s, epm);
         }
@@ -357,21 +366,20 @@ hipError_t with_pattern(const SweepParams& p, F&& f) {
     }
 }
 
-// Elements per lane and lanes of a batched staged launch (the Chebyshev step
-// with dots): the batch's shape, or the shortest tile where the LDS would
-// overflow; calls g(IntC<E>, IntC<NT>).
+// Elements per lane, lanes and columns per element of a batched staged launch
+// (the Chebyshev step with dots): the batch's shape, or the shortest tile where
+// the LDS would overflow; calls g(IntC<E>, IntC<NT>, IntC<W>).
 template <class P, typename T, class G>
 hipError_t batch_tile(const SweepParams& p, G&& g) {
-    constexpr int E0 = sizeof(T) == 8 ? 1 : 2, E1 = 2 * E0;
-    const int e = staged_elems(p);
-    const bool w512 = p.st_nt == 512;
-    auto fits = [](size_t lds) { return lds <= max_lds(); };
-    if (e == E1) {
-        if (w512 && fits(staged_lds_bytes_for<P, T, E1, 512>(false))) return g(IntC<E1>{}, IntC<512>{});
-        if (!w512 && fits(staged_lds_bytes_for<P, T, E1, kBlock>(false))) return g(IntC<E1>{}, IntC<kBlock>{});
-    }
-    if (w512 && fits(staged_lds_bytes_for<P, T, E0, 512>(false))) return g(IntC<E0>{}, IntC<512>{});
-    return g(IntC<E0>{}, IntC<kBlock>{});
+    constexpr int E0 = sizeof(T) == 8 ? 1 : 2;
+    hipError_t e = hipErrorInvalidValue;
+    batch_shape<T>(p, [&](auto ke, auto kn, auto kw) {
+        constexpr int E = decltype(ke)::value, NT = decltype(kn)::value, W = decltype(kw)::value;
+        if (staged_lds_bytes_for<P, T, E, NT, W>(false) <= max_lds()) e = g(ke, kn, kw);
+        else if (staged_lds_bytes_for<P, T, E0, NT, W>(false) <= max_lds()) e = g(IntC<E0>{}, kn, kw);
+        else e = g(IntC<E0>{}, IntC<kBlock>{}, kw);
+    });
+    return e;
 }
 
 }  // namespace
@@ -399,8 +407,9 @@ hipError_t codegen_batch_fill_record(const SweepParams& p, int staged, void* dst
             if (P::NO * p.nb > STAGED_MAX_SITE || (P::NO * p.nb * int(sizeof(cplx<T>))) % 16 != 0)
                 return hipErrorInvalidValue;
             make_kargs<P, T, VT>(p, false, a);
-            return batch_tile<P, T>(p, [&](auto ke, auto kn) -> hipError_t {
-                const int G8 = staged_setup<P, T, VT, decltype(ke)::value, decltype(kn)::value>(p, 1 << 30, true, a);
+            return batch_tile<P, T>(p, [&](auto ke, auto kn, auto kw) -> hipError_t {
+                const int G8 = staged_setup<P, T, VT, decltype(ke)::value, decltype(kn)::value, decltype(kw)::value>(
+                    p, 1 << 30, true, a);
                 std::memcpy(dst, &a, sizeof(a));
                 *nblocks = 8 * G8;
                 return hipSuccess;
@@ -429,12 +438,12 @@ hipError_t batch_function(const SweepParams& p, int staged, bool nocompile, Comp
             lds = 0;
             return function_for(p.cg_src, expr, kBlock, 0, nocompile, c);
         }
-        return batch_tile<P, T>(p, [&](auto ke, auto kn) -> hipError_t {
-            constexpr int E = decltype(ke)::value, NT = decltype(kn)::value;
-            std::snprintf(expr, sizeof expr, "&pv::batch_staged_kernel<pv::PatCG, %s, %s, %d, %uu, %d>", tname<T>(),
-                          tname<VT>(), E, unsigned(EP_STORE_Y | EP_DOTS), NT);
+        return batch_tile<P, T>(p, [&](auto ke, auto kn, auto kw) -> hipError_t {
+            constexpr int E = decltype(ke)::value, NT = decltype(kn)::value, W = decltype(kw)::value;
+            std::snprintf(expr, sizeof expr, "&pv::batch_staged_kernel<pv::PatCG, %s, %s, %d, %uu, %d, %d>", tname<T>(),
+                          tname<VT>(), E, unsigned(EP_STORE_Y | EP_DOTS), NT, W);
             nt = NT;
-            lds = staged_lds_bytes_for<P, T, E, NT>(false);
+            lds = staged_lds_bytes_for<P, T, E, NT, W>(false);
             return function_for(p.cg_src, expr, NT, lds, nocompile, c);
         });
     });

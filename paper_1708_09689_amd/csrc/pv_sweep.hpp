@@ -628,14 +628,35 @@ void batch_sweep_kernel(const KArgs<T, VT>* __restrict__ table, const int* __res
 // one XCD walk a compact block of neighbouring columns side by side and read
 // each other's rows (m -+ 1, w) and x halos from the same L2.
 // ---------------------------------------------------------------------------
-template <typename T, int E, int NT = kBlock>
+// The kernel's elements are 16-byte chunks wherever the layout allows: one
+// complex128 number (W = 1), or the complex64 numbers of two neighbouring
+// columns (W = 2, blocks of at least two columns), with half as many "columns"
+// nb / W.  A lane's LDS read of a neighbour is then 16 bytes, the coefficients
+// serve both columns, and z and acc go from memory to the lane that uses them
+// without LDS (ZR).  Blocks of one complex64 column, and the run-time epilogue,
+// have 8-byte elements, two to a chunk.  E counts complex numbers per lane, EL
+// elements.  Measured on TI, complex64, against one column per element (half
+// as many LDS instructions and row addresses; four numbers per lane no longer
+// spill): step 256x256x64 nb 4 376 -> 352 us (E = 4: 326 -> 293), 64^3 nb 32,
+// E = 4, 154 -> 140; plain 240x240x6 nb 32 242 -> 209.  complex128 without the
+// LDS copies of z and acc: unchanged within 1%.
+template <typename T, int W>
+struct alignas(W * sizeof(cplx<T>)) Elem {
+    cplx<T> v[W];
+};
+
+template <typename T, int E, int NT, int W>
 struct Staged {
     static constexpr int NTH = NT;                           // lanes per workgroup
-    static constexpr int ES = int(sizeof(cplx<T>));
+    static constexpr int EL = E / W;
+    static constexpr int LW = W == 2 ? 1 : 0;
+    static constexpr int ES = int(sizeof(Elem<T, W>));
     static constexpr int CE = 16 / ES;                       // elements per 16-byte chunk
-    static constexpr int TW = NT * E;                        // elements per column tile
+    static constexpr bool ZR = CE == 1;
+    static constexpr int TW = NT * EL;                       // elements per column tile
     static constexpr int TCH = TW / (CE * NT);               // chunks per lane of a row without halo
-    static constexpr int RCH = (TW + 2 * STAGED_MAX_SITE + CE * NT - 1) / (CE * NT);  // with halo
+    static constexpr int RCH = (TW + 2 * STAGED_MAX_SITE / W + CE * NT - 1) / (CE * NT);  // with halo
+    static_assert(E % W == 0 && W * sizeof(cplx<T>) <= 16, "whole elements per lane, at most a chunk each");
     static_assert(TW % (CE * NT) == 0, "a tile must be whole chunks per lane");
     static_assert(NT % 64 == 0 && NT <= 1024, "whole waves");
 };
@@ -660,12 +681,12 @@ __device__ __forceinline__ u32x4 ld_chunk_nt(const void* base, uint32_t boff) {
 // One step's worth of rows in flight: ring row with halo, z and acc_in
 // chunks, field values.  (The side rows of 3D lattices, mostly L2 hits, are
 // loaded one step ahead into a single set of their own.)
-template <class P, typename T, typename VT, int E, int NT>
+template <class P, typename T, typename VT, int E, int NT, int W>
 struct StagedSet {
-    using S = Staged<T, E, NT>;
+    using S = Staged<T, E, NT, W>;
     u32x4 ring[S::RCH];
     u32x4 z[S::TCH];
-    VT v[E];          // stored field entries (converted when handed to LDS)
+    VT v[S::EL];      // stored field entries (converted when handed to LDS)
     int64_t vrow;     // first field entry of the set's row
 };
 
@@ -673,40 +694,42 @@ struct StagedSet {
 // step (P::SIDE_HALO) the tile with the one-site x halo of ring rows.  They
 // are the rows (m -+ 1, w), and for stencils with hops that have a y and a z
 // step (P::SIDE_W) also (m -+ 1, w -+ 1): side row idx(dm, dw).
-template <class P, typename T, int E, int NT>
+template <class P, typename T, int E, int NT, int W>
 struct StagedSide {
+    using S = Staged<T, E, NT, W>;
     static constexpr int NTR = P::DIM == 3 ? (P::SIDE_W ? 6 : 2) : 0;
     __host__ __device__ static constexpr int idx(int dm, int dw) {
         return (dm < 0 ? 0 : 1) + (P::SIDE_W ? 2 * (dw + 1) : 0);
     }
     static constexpr bool HALO = side_halo<P>();
-    static constexpr int SCH = HALO ? Staged<T, E, NT>::RCH : Staged<T, E, NT>::TCH;   // chunks per lane
-    static constexpr int SLEN = HALO ? Staged<T, E, NT>::RCH * NT * Staged<T, E, NT>::CE
-                                     : Staged<T, E, NT>::TW;                         // LDS elements per row
+    static constexpr int SCH = HALO ? S::RCH : S::TCH;                  // chunks per lane
+    static constexpr int SLEN = HALO ? S::RCH * NT * S::CE : S::TW;     // LDS elements per row
     u32x4 side[NTR > 0 ? NTR : 1][SCH];
-    u32x4 acc[Staged<T, E, NT>::TCH];
+    u32x4 acc[S::TCH];
 };
 
 // ZL: the step reads z (every epilogue but the plain sweep with gamma = 0)
-template <class P, typename T, typename VT, int E, bool ACC, int NT, bool ZL = true>
+template <class P, typename T, typename VT, int E, bool ACC, int NT, int W, bool ZL = true>
 struct StagedCtx {
-    using S = Staged<T, E, NT>;
-    using Set = StagedSet<P, T, VT, E, NT>;
-    using Side = StagedSide<P, T, E, NT>;
-    static constexpr int NTR = Side::NTR;
+    using S = Staged<T, E, NT, W>;
+    using El = Elem<T, W>;
+    using Set = StagedSet<P, T, VT, E, NT, W>;
+    using Side = StagedSide<P, T, E, NT, W>;
+    static constexpr int NTR = Side::NTR, EL = S::EL;
     const KArgs<T, VT>& a;
-    cplx<T>* ring;   // [3][seg]
-    cplx<T>* tra;    // [NTR][Side::SLEN]
-    cplx<T>* zl;     // [TW]
-    cplx<T>* al;     // [TW] (ACC only)
-    T* vl;           // [E S::NTH]
+    El* ring;        // [3][seg]
+    El* tra;         // [NTR][Side::SLEN]
+    El* zl;          // [TW] (without ZR)
+    El* al;          // [TW] (ACC only, without ZR)
+    T* vl;           // [EL S::NTH]
     int tid, nch, m, wb;
+    int rowel, site;   // elements per row, per site
     // per walk: byte offsets inside a row of this lane's ring chunks (x
     // wrapped; open boundaries are applied when computing), row chunks and
     // field entries (clamped into the row)
     uint32_t roff[S::RCH] = {};
     uint32_t soff[S::TCH] = {};
-    uint32_t voff[E] = {};
+    uint32_t voff[EL] = {};
     int vshift = 0;  // element -> field entry: log2 of elements per site or per orbital row
 
     __device__ __forceinline__ int64_t row_of(int mm, int ww) const {
@@ -732,14 +755,13 @@ struct StagedCtx {
         return r >= 0 ? a.x + r * a.rowel : a.zero_row;
     }
     __device__ __forceinline__ void setup(int xe0) {
-        const int rowel = a.rowel;
         // chunks past the ring row (tile + halo) repeat its last chunk: every
         // lane loads and stores every chunk without branches, and the
         // repeated addresses add no traffic
 #pragma unroll
         for (int k = 0; k < S::RCH; ++k) {
             const int q = tid + k * S::NTH;
-            int g = xe0 - a.st_site + (q < nch ? q : nch - 1) * S::CE;
+            int g = xe0 - site + (q < nch ? q : nch - 1) * S::CE;
             if (g < 0) g += rowel;
             if (g >= rowel) g %= rowel;
             roff[k] = uint32_t(g) * S::ES;
@@ -753,7 +775,7 @@ struct StagedCtx {
         // row, clamped into the lattice row
         const int vlen = a.pot_mode == 1 ? a.Lx : a.Lx * P::NO;
 #pragma unroll
-        for (int k = 0; k < E; ++k) {
+        for (int k = 0; k < EL; ++k) {
             int r = (xe0 >> vshift) + tid + k * S::NTH;
             if (r >= vlen) r = vlen - 1;
             voff[k] = uint32_t(r);
@@ -779,7 +801,7 @@ struct StagedCtx {
         st.vrow = rw * a.Lx * (a.pot_mode == 1 ? 1 : P::NO);
         const VT* vp = a.field == 1 ? a.V + st.vrow : reinterpret_cast<const VT*>(a.zero_row);
 #pragma unroll
-        for (int k = 0; k < E; ++k) st.v[k] = vp[voff[k]];
+        for (int k = 0; k < EL; ++k) st.v[k] = vp[voff[k]];
     }
     // Side rows (m -+ 1, w_row) (and (m -+ 1, w_row -+ 1) for SIDE_W),
     // w_row clamped to the walk (3D lattices).
@@ -806,7 +828,7 @@ struct StagedCtx {
         }
     }
     __device__ __forceinline__ void commit_side(const Side& sd) const {
-        if constexpr (ACC) {
+        if constexpr (ACC && !S::ZR) {
             u32x4* da = reinterpret_cast<u32x4*>(al);
 #pragma unroll
             for (int k = 0; k < S::TCH; ++k) da[tid + k * S::NTH] = sd.acc[k];
@@ -825,7 +847,7 @@ struct StagedCtx {
         u32x4* d = reinterpret_cast<u32x4*>(ring + slot * a.st_seg);
 #pragma unroll
         for (int k = 0; k < S::RCH; ++k) d[tid + k * S::NTH] = st.ring[k];
-        if constexpr (ZL) {
+        if constexpr (ZL && !S::ZR) {
             u32x4* dz = reinterpret_cast<u32x4*>(zl);
 #pragma unroll
             for (int k = 0; k < S::TCH; ++k) dz[tid + k * S::NTH] = st.z[k];
@@ -835,13 +857,13 @@ struct StagedCtx {
             // orbital row) are generated, not one per lane and element
             const int nent = S::TW >> vshift;
 #pragma unroll
-            for (int k = 0; k < E; ++k) {
+            for (int k = 0; k < EL; ++k) {
                 const int q = tid + k * S::NTH;
                 if (q < nent) vl[q] = field_at(a, st.vrow + voff[k]);
             }
         } else {
 #pragma unroll
-            for (int k = 0; k < E; ++k) vl[tid + k * S::NTH] = T(st.v[k]);
+            for (int k = 0; k < EL; ++k) vl[tid + k * S::NTH] = T(st.v[k]);
         }
     }
     // Ring row (m, ww) alone into a slot (walk prologue).
@@ -857,17 +879,19 @@ struct StagedCtx {
 
 // LDS of a staged workgroup: three ring rows with halo (slots padded to
 // whole chunks per lane), the side rows of 3D lattices, z (and acc_in) of
-// the tile, and the field of its orbital rows (padded to E per lane).
-template <typename T, int E, int NT>
+// the tile without ZR, and the field of its orbital rows (padded to EL per
+// lane).
+template <typename T, int E, int NT, int W>
 __host__ __device__ constexpr int staged_seg() {
-    return Staged<T, E, NT>::RCH * NT * Staged<T, E, NT>::CE;
+    return Staged<T, E, NT, W>::RCH * NT * Staged<T, E, NT, W>::CE;
 }
-template <class P, typename T, int E, int NT>
+template <class P, typename T, int E, int NT, int W>
 __host__ __device__ constexpr size_t staged_table_offset(bool acc) {
-    return (size_t(3 * staged_seg<T, E, NT>() + StagedSide<P, T, E, NT>::NTR * StagedSide<P, T, E, NT>::SLEN +
-                   (1 + (acc ? 1 : 0)) * Staged<T, E, NT>::TW) *
-                Staged<T, E, NT>::ES +
-            size_t(E * NT) * sizeof(T) + 15) / 16 * 16;
+    using S = Staged<T, E, NT, W>;
+    using Side = StagedSide<P, T, E, NT, W>;
+    return (size_t(3 * staged_seg<T, E, NT, W>() + Side::NTR * Side::SLEN +
+                   (S::ZR ? 0 : 1 + (acc ? 1 : 0)) * S::TW) * S::ES +
+            size_t(S::EL * NT) * sizeof(T) + 15) / 16 * 16;
 }
 // Generic stencils also keep their block entries in LDS: values, then
 // offsets, row starts and columns.
@@ -877,20 +901,56 @@ struct StagedTable {
     static constexpr int NPTR = (PV_MAX_TERMS_K + 1) * P::NO + 1;
     static constexpr int NINT = 3 * PV_MAX_TERMS_K + NPTR + GMAX;
 };
-template <class P, typename T, int E, int NT>
+template <class P, typename T, int E, int NT, int W>
 __host__ __device__ constexpr size_t staged_lds_bytes_for(bool acc) {
-    return staged_table_offset<P, T, E, NT>(acc) +
+    return staged_table_offset<P, T, E, NT, W>(acc) +
            (P::FAMILY == FAM_GENERIC
                 ? StagedTable<P>::GMAX * sizeof(cplx<T>) + StagedTable<P>::NINT * sizeof(int)
                 : 0);
 }
 
-template <class P, typename T, typename VT, int E, unsigned EPM, int NT>
+// Epilogue of the specialised kernels (uniform alpha, beta, gamma): the
+// operations of epilogue_ep, with whole elements loaded and stored.
+template <unsigned EPM, typename T, typename VT, int W>
+__device__ __forceinline__ void staged_epilogue(const KArgs<T, VT>& a, int64_t e, const Elem<T, W>& x,
+                                                const Elem<T, W>& z, const Elem<T, W>& acc, const Elem<T, W>& h, T alT,
+                                                T gaT, T er, T ei, double (&dxx)[W], double (&dxr)[W],
+                                                double (&dxi)[W], double (&dyy)[W]) {
+    using V = T __attribute__((ext_vector_type(2 * W)));
+    V yo, ao;
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        T yr = alT * h.v[q].re, yi = alT * h.v[q].im;
+        yr += (gaT != T(0)) ? gaT * z.v[q].re : T(0);
+        yi += (gaT != T(0)) ? gaT * z.v[q].im : T(0);
+        yo[2 * q] = yr;
+        yo[2 * q + 1] = yi;
+        if constexpr ((EPM & EP_ACC_ADD) != 0u) {
+            ao[2 * q] = acc.v[q].re + er * yr - ei * yi;
+            ao[2 * q + 1] = acc.v[q].im + er * yi + ei * yr;
+        }
+        if constexpr ((EPM & EP_DOTS) != 0u) {
+            const double xr = double(x.v[q].re), xi = double(x.v[q].im);
+            const double dyr = double(yr), dyi = double(yi);
+            dxx[q] += xr * xr + xi * xi;
+            dxr[q] += xr * dyr + xi * dyi;
+            dxi[q] += xr * dyi - xi * dyr;
+            dyy[q] += dyr * dyr + dyi * dyi;
+        }
+    }
+    if constexpr ((EPM & EP_STORE_Y) != 0u) __builtin_nontemporal_store(yo, reinterpret_cast<V*>(a.y + e));
+    if constexpr ((EPM & EP_ACC_ADD) != 0u) __builtin_nontemporal_store(ao, reinterpret_cast<V*>(a.acc_out + e));
+}
+
+template <class P, typename T, typename VT, int E, unsigned EPM, int NT, int W>
 __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, int part, int jb, int G) {
-    using S = Staged<T, E, NT>;
+    using S = Staged<T, E, NT, W>;
+    using El = Elem<T, W>;
+    static_assert(EPM != 0u || W == 1, "the run-time epilogue has elements of one column");
+    constexpr int EL = S::EL;
     constexpr bool ACC = EPM == 0u || (EPM & EP_ACC_ADD) != 0u;
     constexpr bool ZL = (EPM & EP_NO_Z) == 0u;
-    using Ctx = StagedCtx<P, T, VT, E, ACC, NT, ZL>;
+    using Ctx = StagedCtx<P, T, VT, E, ACC, NT, W, ZL>;
     using Set = typename Ctx::Set;
     constexpr int NO = P::NO;
     constexpr int NTR = Ctx::NTR;
@@ -898,10 +958,11 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
     extern __shared__ __align__(16) unsigned char smem[];
     const unsigned ep = EPM ? EPM : a.ep;
     const int tid = threadIdx.x;
-    const int nb = a.nb;
+    // in elements of W columns
+    const int nb = a.nb >> S::LW, lognb = a.lognb - S::LW, logsite = a.logsite - S::LW;
     const int c = tid & (nb - 1);
-    const int o = (tid >> a.lognb) & (NO - 1);
-    const int site = a.st_site;
+    const int o = (tid >> lognb) & (NO - 1);
+    const int site = a.st_site >> S::LW, rowel = a.rowel >> S::LW;
 
     // per-column alpha, beta, gamma only in the run-time epilogue (the
     // specialised ones are launched with uniform values)
@@ -921,12 +982,12 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
     T cre[NS > 0 ? NS : 1], cim[NS > 0 ? NS : 1];
     int dq[NS > 0 ? NS : 1];
     slot_coefficients<P, T, NS>(a.coef, o, nb, cre, cim, dq);
-    double dxx = 0.0, dxr = 0.0, dxi = 0.0, dyy = 0.0;
+    double dxx[W] = {}, dxr[W] = {}, dxi[W] = {}, dyy[W] = {};
 
     // generic stencils: offsets and the nonzero entries of every block row
     // (packed by the host after the offsets and the dense blocks) in LDS
     using Tab = StagedTable<P>;
-    cplx<T>* g_val = reinterpret_cast<cplx<T>*>(smem + staged_table_offset<P, T, E, NT>(ACC));
+    cplx<T>* g_val = reinterpret_cast<cplx<T>*>(smem + staged_table_offset<P, T, E, NT, W>(ACC));
     int* g_off = reinterpret_cast<int*>(g_val + Tab::GMAX);
     int* g_ptr = g_off + 3 * PV_MAX_TERMS_K;
     int* g_col = g_ptr + Tab::NPTR;
@@ -944,12 +1005,13 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
         __syncthreads();
     }
 
-    Ctx cx{a, reinterpret_cast<cplx<T>*>(smem), nullptr, nullptr, nullptr, nullptr, tid, (S::TW + 2 * site) / S::CE, 0, 0};
-    cx.vshift = a.pot_mode == 1 ? a.logsite : a.lognb;
+    Ctx cx{a, reinterpret_cast<El*>(smem), nullptr, nullptr, nullptr, nullptr, tid, (S::TW + 2 * site) / S::CE, 0, 0,
+           rowel, site};
+    cx.vshift = a.pot_mode == 1 ? logsite : lognb;
     cx.tra = cx.ring + 3 * a.st_seg;
     cx.zl = cx.tra + NTR * Ctx::Side::SLEN;
-    cx.al = cx.zl + S::TW;
-    cx.vl = reinterpret_cast<T*>(cx.al + (ACC ? S::TW : 0));
+    cx.al = cx.zl + (S::ZR ? 0 : S::TW);
+    cx.vl = reinterpret_cast<T*>(cx.al + (ACC && !S::ZR ? S::TW : 0));
 
     // this part's ranges of m and w
     int m0 = 0, m1 = a.st_Lm, wA = 0, wB = a.st_Lw;
@@ -994,6 +1056,17 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
         cx.issue(A, wa + 1, wa);
         cx.commit(A, 2);
         cx.commit_side(SD);
+        El zc[EL], ac[EL];   // z and acc of the step at hand (ZR)
+        auto take = [&](const Set& st) {
+            if constexpr (S::ZR) {
+#pragma unroll
+                for (int k = 0; k < EL; ++k) {
+                    if constexpr (ZL) zc[k] = __builtin_bit_cast(El, st.z[k]);
+                    if constexpr (ACC) ac[k] = __builtin_bit_cast(El, SD.acc[k]);
+                }
+            }
+        };
+        take(A);
         cx.issue(B, wa + 2, wa + 1);
         lds_barrier();
 
@@ -1006,24 +1079,27 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
             const int w = wa + s;
             cx.issue_side(SD, w + 1);
             cx.issue(nx, s + 2 < nsteps ? w + 3 : w + 1, w + 2);
-            const cplx<T>* rm = cx.ring + (s % 3) * a.st_seg + site;
-            const cplx<T>* r0 = cx.ring + ((s + 1) % 3) * a.st_seg + site;
-            const cplx<T>* rp = cx.ring + ((s + 2) % 3) * a.st_seg + site;
+            const El* rm = cx.ring + (s % 3) * a.st_seg + site;
+            const El* r0 = cx.ring + ((s + 1) % 3) * a.st_seg + site;
+            const El* rp = cx.ring + ((s + 2) % 3) * a.st_seg + site;
             const int64_t rowi = cx.row_of(cx.m, w);
             const int64_t rb = rowi * a.rowel;
-            T yr[E], yi[E];
-            cplx<T> xs_[E], zv[E], av[E];
+            El hv[EL], xs_[EL], zv[EL], av[EL];
 #pragma unroll
-            for (int k = 0; k < E; ++k) {
+            for (int k = 0; k < EL; ++k) {
                 const int l = tid + k * NT;
                 const int xe = xe0 + l;
-                const int x = xe >> a.logsite;
+                const int x = xe >> logsite;
                 const bool xlo = a.px || x > 0, xhi = a.px || x < a.Lx - 1;
-                const cplx<T> xc = r0[l];
+                const El xc = r0[l];
                 const T vs = a.field != 0 ? cx.vl[l >> cx.vshift] : T(0);
                 const T d = dgr - beT + vs;
-                T hr = d * xc.re - dgi * xc.im;
-                T hi = d * xc.im + dgi * xc.re;
+                T hr[W], hi[W];
+#pragma unroll
+                for (int q = 0; q < W; ++q) {
+                    hr[q] = d * xc.v[q].re - dgi * xc.v[q].im;
+                    hi[q] = d * xc.v[q].im + dgi * xc.v[q].re;
+                }
                 if constexpr (GEN) {
                     // runtime terms: rows (m, w + dw) from the ring with the x
                     // halo, rows (m -+ 1, w) from the side rows (with the x halo
@@ -1033,34 +1109,39 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
                         const int dx = g_off[3 * tb], dm = g_off[3 * tb + 1], dw = g_off[3 * tb + 2];
                         // side rows start at the tile (no halo) or one site before it
                         constexpr int side0 = Ctx::Side::HALO ? 1 : 0;
-                        const cplx<T>* rw = (dm != 0 ? cx.tra + (dm < 0 ? 0 : Ctx::Side::SLEN) + side0 * site
-                                                     : (dw < 0 ? rm : (dw > 0 ? rp : r0))) + l + dx * site;
+                        const El* rw = (dm != 0 ? cx.tra + (dm < 0 ? 0 : Ctx::Side::SLEN) + side0 * site
+                                                : (dw < 0 ? rm : (dw > 0 ? rp : r0))) + l + dx * site;
                         const bool ok = dx < 0 ? xlo : (dx > 0 ? xhi : true);
                         const int e0 = g_ptr[tb * NO + o], e1 = g_ptr[tb * NO + o + 1];
-                        for (int e = e0; e < e1; ++e)
-                            mac<T>(hr, hi, CC, g_val[e].re, g_val[e].im, zero_unless(ok, rw[(g_col[e] - o) * nb]));
+                        for (int e = e0; e < e1; ++e) {
+                            const El v = rw[(g_col[e] - o) * nb];
+#pragma unroll
+                            for (int q = 0; q < W; ++q)
+                                mac<T>(hr[q], hi[q], CC, g_val[e].re, g_val[e].im, zero_unless(ok, v.v[q]));
+                        }
                     }
                     const int e0 = g_ptr[a.n_terms * NO + o], e1 = g_ptr[a.n_terms * NO + o + 1];
-                    for (int e = e0; e < e1; ++e)
-                        mac<T>(hr, hi, CC, g_val[e].re, g_val[e].im, r0[l + (g_col[e] - o) * nb]);
+                    for (int e = e0; e < e1; ++e) {
+                        const El v = r0[l + (g_col[e] - o) * nb];
+#pragma unroll
+                        for (int q = 0; q < W; ++q) mac<T>(hr[q], hi[q], CC, g_val[e].re, g_val[e].im, v.v[q]);
+                    }
                 } else {
                     sfor<NS>([&](auto jj) {
                         constexpr int jx = decltype(jj)::value;
                         constexpr int t = SL.t[jx];
                         const int dqj = SL.same[jx] ? 0 : dq[jx];   // constant 0 for own-orbital slots
-                        cplx<T> v;
+                        El v;
+                        constexpr int tt = t < P::NT ? t : 0;
+                        constexpr int dx = t < P::NT ? P::off[tt][0] : 0;
                         if constexpr (t == P::NT) {
                             v = r0[l + dqj];
                         } else {
-                            constexpr int tt = t < P::NT ? t : 0;
-                            constexpr int dx = P::off[tt][0];
                             constexpr int dm = P::DIM == 3 ? P::off[tt][1] : 0;
                             constexpr int dw = P::DIM == 3 ? P::off[tt][2] : P::off[tt][1];
                             if constexpr (dm == 0) {
-                                const cplx<T>* rw = dw < 0 ? rm : (dw > 0 ? rp : r0);
+                                const El* rw = dw < 0 ? rm : (dw > 0 ? rp : r0);
                                 v = rw[l + dx * site + dqj];
-                                if constexpr (dx < 0) v = zero_unless(xlo, v);
-                                if constexpr (dx > 0) v = zero_unless(xhi, v);
                             } else {
                                 // side rows start at the tile, or one site
                                 // before it in the instance with the halo
@@ -1069,30 +1150,43 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
                                 static_assert(dx == 0 || HALO, "x steps on side rows need their halo");
                                 constexpr int h = Ctx::Side::idx(dm, dw);
                                 v = cx.tra[h * Ctx::Side::SLEN + (HALO ? site : 0) + l + dx * site + dqj];
-                                if constexpr (dx < 0) v = zero_unless(xlo, v);
-                                if constexpr (dx > 0) v = zero_unless(xhi, v);
                             }
                         }
-                        mac<T>(hr, hi, SL.kind[jx], cre[jx], cim[jx], v);
+#pragma unroll
+                        for (int q = 0; q < W; ++q) {
+                            cplx<T> u = v.v[q];
+                            if constexpr (dx < 0) u = zero_unless(xlo, u);
+                            if constexpr (dx > 0) u = zero_unless(xhi, u);
+                            mac<T>(hr[q], hi[q], SL.kind[jx], cre[jx], cim[jx], u);
+                        }
                     });
                 }
                 xs_[k] = xc;
-                yr[k] = hr;
-                yi[k] = hi;
-                zv[k] = ZL ? cx.zl[l] : cplx<T>{T(0), T(0)};
-                av[k] = ACC ? cx.al[l] : cplx<T>{T(0), T(0)};
+#pragma unroll
+                for (int q = 0; q < W; ++q) hv[k].v[q] = cplx<T>{hr[q], hi[q]};
+                if constexpr (ZL) zv[k] = S::ZR ? zc[k] : cx.zl[l];
+                else zv[k] = El{};
+                if constexpr (ACC) av[k] = S::ZR ? ac[k] : cx.al[l];
+                else av[k] = El{};
             }
             lds_barrier();
             cx.commit(cur, (s + 3) % 3);
             cx.commit_side(SD);
+            take(cur);
 #pragma unroll
-            for (int k = 0; k < E; ++k) {
+            for (int k = 0; k < EL; ++k) {
                 const int xe = xe0 + tid + k * NT;
-                if (xe < a.rowel) {
-                    const int64_t st = rowi * a.Lx + (xe >> a.logsite);
-                    const int64_t gidx = a.ggroup == nb ? st * NO + o : st;
-                    epilogue_ep(a, ep, rb + xe, gidx, tid & (a.ggroup - 1), xs_[k], zv[k], av[k], yr[k], yi[k], alT,
-                                gaT, er, ei, e0r, e0i, c, dxx, dxr, dxi, dyy);
+                if (xe < rowel) {
+                    if constexpr (EPM == 0u) {
+                        const int64_t st = rowi * a.Lx + (xe >> logsite);
+                        const int64_t gidx = a.ggroup == a.nb ? st * NO + o : st;
+                        epilogue_ep(a, ep, rb + xe, gidx, tid & (a.ggroup - 1), xs_[k].v[0], zv[k].v[0], av[k].v[0],
+                                    hv[k].v[0].re, hv[k].v[0].im, alT, gaT, er, ei, e0r, e0i, c, dxx[0], dxr[0],
+                                    dxi[0], dyy[0]);
+                    } else {
+                        staged_epilogue<EPM>(a, rb + (int64_t(xe) << S::LW), xs_[k], zv[k], av[k], hv[k], alT, gaT, er,
+                                             ei, dxx, dxr, dxi, dyy);
+                    }
                 }
             }
             lds_barrier();
@@ -1106,27 +1200,33 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
     }
 
     if (ep & EP_DOTS) {
-        for (int mm = nb; mm < 64; mm <<= 1) {
-            dxx += __shfl_xor(dxx, mm);
-            dxr += __shfl_xor(dxr, mm);
-            dxi += __shfl_xor(dxi, mm);
-            dyy += __shfl_xor(dyy, mm);
-        }
+#pragma unroll
+        for (int q = 0; q < W; ++q)
+            for (int mm = nb; mm < 64; mm <<= 1) {
+                dxx[q] += __shfl_xor(dxx[q], mm);
+                dxr[q] += __shfl_xor(dxr[q], mm);
+                dxi[q] += __shfl_xor(dxi[q], mm);
+                dyy[q] += __shfl_xor(dyy[q], mm);
+            }
         __syncthreads();
         double* red = reinterpret_cast<double*>(smem);   // the ring is free after the last barrier
         const int wave = tid >> 6, lane = tid & 63;
         if (lane < nb) {
-            red[(wave * PV_MAX_NB_K + lane) * 4 + 0] = dxx;
-            red[(wave * PV_MAX_NB_K + lane) * 4 + 1] = dxr;
-            red[(wave * PV_MAX_NB_K + lane) * 4 + 2] = dxi;
-            red[(wave * PV_MAX_NB_K + lane) * 4 + 3] = dyy;
+#pragma unroll
+            for (int q = 0; q < W; ++q) {
+                double* r = red + (wave * PV_MAX_NB_K + lane * W + q) * 4;
+                r[0] = dxx[q];
+                r[1] = dxr[q];
+                r[2] = dxi[q];
+                r[3] = dyy[q];
+            }
         }
         __syncthreads();
-        if (tid < nb * 4) {
+        if (tid < a.nb * 4) {
             const int cc = tid >> 2, q = tid & 3;
             double sum = 0.0;
             for (int wv = 0; wv < NT / 64; ++wv) sum += red[(wv * PV_MAX_NB_K + cc) * 4 + q];
-            a.partials[((size_t)b_out * nb + cc) * 4 + q] = sum;
+            a.partials[((size_t)b_out * a.nb + cc) * 4 + q] = sum;
         }
     }
 }
@@ -1134,7 +1234,7 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
 // Staged sweep over a batch of lattices in one launch: instance i owns the
 // workgroups [inst_block0[i], inst_block0[i+1]), a multiple of 8 starting at
 // a multiple of 8, split into its 8 XCD parts like a single-lattice launch.
-template <class P, typename T, typename VT, int E, unsigned EPM, int NT = kBlock>
+template <class P, typename T, typename VT, int E, unsigned EPM, int NT, int W>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(PV_STAGED_WAVES_PER_EU)))
 void batch_staged_kernel(const KArgs<T, VT>* __restrict__ table, const int* __restrict__ block_inst,
                          const int* __restrict__ inst_block0, int64_t part_off) {
@@ -1145,17 +1245,17 @@ void batch_staged_kernel(const KArgs<T, VT>* __restrict__ table, const int* __re
     KArgs<T, VT> a = table[i];
     a.partials += part_off;
     const int lb = b - b0;
-    staged_block<P, T, VT, E, EPM, NT>(a, b, lb & 7, lb >> 3, (b1 - b0) >> 3);
+    staged_block<P, T, VT, E, EPM, NT, W>(a, b, lb & 7, lb >> 3, (b1 - b0) >> 3);
 }
 
 // NT lanes per workgroup (256, or 512 for twice the tile length: half the
 // relative x halo, one workgroup per CU at the larger shapes)
-template <class P, typename T, typename VT, int E, unsigned EPM, int NT>
+template <class P, typename T, typename VT, int E, unsigned EPM, int NT, int W>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(PV_STAGED_WAVES_PER_EU)))
 void staged_kernel(KArgs<T, VT> a) {
     const bool p8 = a.st_parts == 8;
     const int b = blockIdx.x, g = gridDim.x;
-    staged_block<P, T, VT, E, EPM, NT>(a, b, p8 ? (b & 7) : 0, p8 ? (b >> 3) : b, p8 ? (g >> 3) : g);
+    staged_block<P, T, VT, E, EPM, NT, W>(a, b, p8 ? (b & 7) : 0, p8 ? (b >> 3) : b, p8 ? (g >> 3) : g);
 }
 
 #ifndef PV_RTC
@@ -1266,17 +1366,17 @@ int env_int(const char* name, int dflt) {
 }
 
 // LDS of a staged kernel instance (independent of nb: tiles are elements)
-template <class P, typename T, int E, unsigned EPM, int NT = kBlock>
+template <class P, typename T, int E, unsigned EPM, int NT, int W>
 size_t staged_lds_bytes() {
-    return staged_lds_bytes_for<P, T, E, NT>(EPM == 0u || (EPM & EP_ACC_ADD) != 0u);
+    return staged_lds_bytes_for<P, T, E, NT, W>(EPM == 0u || (EPM & EP_ACC_ADD) != 0u);
 }
 
-template <class P, typename T, typename VT, int E, int NT = kBlock>
+template <class P, typename T, typename VT, int E, int NT, int W>
 int staged_setup(const SweepParams& p, int G8, bool full_walk, KArgs<T, VT>& a) {
-    using S = Staged<T, E, NT>;
+    constexpr int TW = NT * E;   // complex numbers of a column tile
     a.st_site = P::NO * p.nb;
-    a.st_seg = staged_seg<T, E, NT>();   // ring slot; its first TW + 2 site elements hold the row
-    a.st_nxs = (a.rowel + S::TW - 1) / S::TW;
+    a.st_seg = staged_seg<T, E, NT, W>();   // ring slot; its first elements hold the tile and two sites
+    a.st_nxs = (a.rowel + TW - 1) / TW;
     if (P::DIM == 3) {
         a.st_Lm = a.Ly; a.st_Lw = a.Lz; a.st_pm = a.py; a.st_pw = a.pz;
     } else {
@@ -1300,7 +1400,7 @@ int staged_setup(const SweepParams& p, int G8, bool full_walk, KArgs<T, VT>& a) 
     }
     const int items = nW < 1 ? 1 : ((nW + a.st_C - 1) / a.st_C) * cols;
     if (G8 > items) G8 = items;
-    int bx = int(std::lround(std::sqrt(double(G8) * a.st_site / S::TW)));
+    int bx = int(std::lround(std::sqrt(double(G8) * a.st_site / TW)));
     if (bx > a.st_nxs) bx = a.st_nxs;
     if (bx < 1) bx = 1;
     a.st_Bm = p.st_Bm > 0 ? p.st_Bm : (G8 / bx > 1 ? G8 / bx : 1);
@@ -1308,34 +1408,56 @@ int staged_setup(const SweepParams& p, int G8, bool full_walk, KArgs<T, VT>& a) 
     return G8;
 }
 
-template <class P, typename T, typename VT, int E, unsigned EPM, int NT = kBlock>
-hipError_t launch_staged(SweepParams& p, int num_cus, hipStream_t s) {
+template <class P, typename T, typename VT, int E, unsigned EPM, int NT, int W>
+hipError_t launch_staged_w(SweepParams& p, int num_cus, hipStream_t s) {
     KArgs<T, VT> a;
     make_kargs<P, T, VT>(p, false, a);
     // LDS size and workgroups resident per CU: fixed per kernel instance,
     // set up once (thread-safe initialisation of the local static)
     static const std::pair<hipError_t, int> occ_res = [] {
-        const size_t bytes = staged_lds_bytes<P, T, E, EPM, NT>();
+        const size_t bytes = staged_lds_bytes<P, T, E, EPM, NT, W>();
         if (bytes > 65536) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&staged_kernel<P, T, VT, E, EPM, NT>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
+            const hipError_t e = hipFuncSetAttribute(
+                reinterpret_cast<const void*>(&staged_kernel<P, T, VT, E, EPM, NT, W>),
+                hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
             if (e != hipSuccess) return std::make_pair(e, 0);
         }
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, staged_kernel<P, T, VT, E, EPM, NT>, NT, bytes) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, staged_kernel<P, T, VT, E, EPM, NT, W>, NT, bytes) !=
                 hipSuccess || n < 1)
             n = 1;
         return std::make_pair(hipSuccess, n);
     }();
     if (occ_res.first != hipSuccess) return occ_res.first;
     const int occ = occ_res.second;
-    const size_t lds = staged_lds_bytes<P, T, E, EPM, NT>();
+    const size_t lds = staged_lds_bytes<P, T, E, EPM, NT, W>();
     int G8 = p.st_G8 > 0 ? p.st_G8 : (num_cus >= 8 ? num_cus / 8 : 1) * occ;
     if (G8 > 256) G8 = 256;
-    G8 = staged_setup<P, T, VT, E, NT>(p, G8, false, a);
+    G8 = staged_setup<P, T, VT, E, NT, W>(p, G8, false, a);
     p.grid = 8 * G8;
-    hipLaunchKernelGGL((staged_kernel<P, T, VT, E, EPM, NT>), dim3(p.grid), dim3(NT), lds, s, a);
+    hipLaunchKernelGGL((staged_kernel<P, T, VT, E, EPM, NT, W>), dim3(p.grid), dim3(NT), lds, s, a);
     return hipGetLastError();
+}
+
+// Whether a block's vectors can be taken as 16-byte elements of two complex64
+// columns: whole pairs of columns, and everything the epilogue touches aligned
+// (x is checked with every staged launch).
+template <typename T>
+bool paired(const SweepParams& p) {
+    if (sizeof(T) != 4 || p.nb < 2) return false;
+    const uintptr_t all = reinterpret_cast<uintptr_t>(p.x) | reinterpret_cast<uintptr_t>(p.z) |
+                          reinterpret_cast<uintptr_t>(p.y) |
+                          ((p.ep & EP_ACC_ADD) ? reinterpret_cast<uintptr_t>(p.acc_in) |
+                                                     reinterpret_cast<uintptr_t>(p.acc_out) : 0);
+    return (all & 15) == 0;
+}
+
+template <class P, typename T, typename VT, int E, unsigned EPM, int NT = kBlock>
+hipError_t launch_staged(SweepParams& p, int num_cus, hipStream_t s) {
+    if constexpr (sizeof(T) == 4 && EPM != 0u) {
+        if (paired<T>(p)) return launch_staged_w<P, T, VT, E, EPM, NT, 2>(p, num_cus, s);
+    }
+    return launch_staged_w<P, T, VT, E, EPM, NT, 1>(p, num_cus, s);
 }
 
 // Epilogue specialisations of the staged kernel: the Chebyshev step with
@@ -1465,6 +1587,30 @@ hipError_t dispatch_types(int dtype, int vtype, F&& f) {
     return f(Tag<float>{}, Tag<float>{});
 }
 
+// Calls f(IntC<E>, IntC<NT>, IntC<W>) for a batched staged launch: elements per
+// lane, lanes and columns per element (two for complex64 blocks of at least two
+// columns: a batch's vectors are 16-byte aligned).
+template <typename T, class F>
+void batch_shape(const SweepParams& p, F&& f) {
+    constexpr int E0 = sizeof(T) == 8 ? 1 : 2, E1 = 2 * E0;
+    const bool e1 = staged_elems(p) == E1, w512 = p.st_nt == 512;
+    auto lanes = [&](auto ke) {
+        auto go = [&](auto kn) {
+            if constexpr (sizeof(T) == 4) {
+                if (p.nb >= 2) {
+                    f(ke, kn, IntC<2>{});
+                    return;
+                }
+            }
+            f(ke, kn, IntC<1>{});
+        };
+        if (w512) go(IntC<512>{});
+        else go(IntC<kBlock>{});
+    };
+    if (e1) lanes(IntC<E1>{});
+    else lanes(IntC<E0>{});
+}
+
 // Argument record of one instance of a batched sweep and its workgroup count.
 template <class P>
 hipError_t batch_fill_record_fam(const SweepParams& p, int staged, void* dst, int* nblocks) {
@@ -1478,19 +1624,11 @@ hipError_t batch_fill_record_fam(const SweepParams& p, int staged, void* dst, in
                 if (P::NO * p.nb > STAGED_MAX_SITE || (P::NO * p.nb * int(sizeof(cplx<T>))) % 16 != 0)
                     return hipErrorInvalidValue;
                 make_kargs<P, T, VT>(p, false, a);
-                const int e = staged_elems(p);
-                const bool w512 = p.st_nt == 512;
-                int G8;
-                if constexpr (sizeof(T) == 8)
-                    G8 = e == 2 ? (w512 ? staged_setup<P, T, VT, 2, 512>(p, 1 << 30, true, a)
-                                        : staged_setup<P, T, VT, 2>(p, 1 << 30, true, a))
-                                : (w512 ? staged_setup<P, T, VT, 1, 512>(p, 1 << 30, true, a)
-                                        : staged_setup<P, T, VT, 1>(p, 1 << 30, true, a));
-                else
-                    G8 = e == 4 ? (w512 ? staged_setup<P, T, VT, 4, 512>(p, 1 << 30, true, a)
-                                        : staged_setup<P, T, VT, 4>(p, 1 << 30, true, a))
-                                : (w512 ? staged_setup<P, T, VT, 2, 512>(p, 1 << 30, true, a)
-                                        : staged_setup<P, T, VT, 2>(p, 1 << 30, true, a));
+                int G8 = 0;
+                batch_shape<T>(p, [&](auto ke, auto kn, auto kw) {
+                    G8 = staged_setup<P, T, VT, decltype(ke)::value, decltype(kn)::value, decltype(kw)::value>(
+                        p, 1 << 30, true, a);
+                });
                 std::memcpy(dst, &a, sizeof(a));
                 *nblocks = 8 * G8;
                 return hipSuccess;
@@ -1513,34 +1651,22 @@ hipError_t launch_batch_sweep_fam(const SweepParams& p, int staged, const void* 
         if constexpr (P::FAMILY != FAM_GENERIC) {
             if (staged) {
                 constexpr unsigned KPM = EP_STORE_Y | EP_DOTS;
-                auto go = [&](auto ke, auto kn) -> hipError_t {
-                    constexpr int E = decltype(ke)::value;
-                    constexpr int NT = decltype(kn)::value;
-                    const size_t lds = staged_lds_bytes<P, T, E, KPM, NT>();
-                    if (lds > 65536) {
-                        hipError_t e = hipFuncSetAttribute(
-                            reinterpret_cast<const void*>(&batch_staged_kernel<P, T, VT, E, KPM, NT>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-                        if (e != hipSuccess) return e;
-                    }
-                    hipLaunchKernelGGL((batch_staged_kernel<P, T, VT, E, KPM, NT>), dim3(grid), dim3(NT), lds, s,
-                                       static_cast<const KArgs<T, VT>*>(table), block_inst, inst_block0, part_off);
-                    return hipGetLastError();
-                };
                 if (p.ep != KPM) return hipErrorInvalidValue;
-                const int e = staged_elems(p);
-                using I = std::integral_constant<int, 1>;
-                using I2 = std::integral_constant<int, 2>;
-                using I4 = std::integral_constant<int, 4>;
-                using N256 = std::integral_constant<int, kBlock>;
-                using N512 = std::integral_constant<int, 512>;
-                if constexpr (sizeof(T) == 8) {
-                    if (p.st_nt == 512) return e == 2 ? go(I2{}, N512{}) : go(I{}, N512{});
-                    return e == 2 ? go(I2{}, N256{}) : go(I{}, N256{});
-                } else {
-                    if (p.st_nt == 512) return e == 4 ? go(I4{}, N512{}) : go(I2{}, N512{});
-                    return e == 4 ? go(I4{}, N256{}) : go(I2{}, N256{});
-                }
+                hipError_t e = hipSuccess;
+                batch_shape<T>(p, [&](auto ke, auto kn, auto kw) {
+                    constexpr int E = decltype(ke)::value, NT = decltype(kn)::value, W = decltype(kw)::value;
+                    const size_t lds = staged_lds_bytes<P, T, E, KPM, NT, W>();
+                    if (lds > 65536) {
+                        e = hipFuncSetAttribute(
+                            reinterpret_cast<const void*>(&batch_staged_kernel<P, T, VT, E, KPM, NT, W>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+                        if (e != hipSuccess) return;
+                    }
+                    hipLaunchKernelGGL((batch_staged_kernel<P, T, VT, E, KPM, NT, W>), dim3(grid), dim3(NT), lds, s,
+                                       static_cast<const KArgs<T, VT>*>(table), block_inst, inst_block0, part_off);
+                    e = hipGetLastError();
+                });
+                return e;
             }
         }
         hipLaunchKernelGGL((batch_sweep_kernel<P, T, VT>), dim3(grid), dim3(kBlock), 0, s,
