@@ -1465,11 +1465,11 @@ hipError_t launch_staged(SweepParams& p, int num_cus, hipStream_t s) {
 // or Chebyshev step without dots (with gamma = 0: no z stream at all), and
 // every other combination with the flags read at run time.
 template <class P, typename T, typename VT, int E>
-hipError_t launch_staged_ep(SweepParams& p, int num_cus, hipStream_t s) {
+hipError_t launch_staged_ep(SweepParams& p, int nt, int num_cus, hipStream_t s) {
     constexpr unsigned KPM = EP_STORE_Y | EP_DOTS, SERIES = EP_STORE_Y | EP_ACC_ADD, PLAIN = EP_STORE_Y;
     if (p.colp == nullptr) {
         if constexpr (P::FAMILY != FAM_GENERIC) {
-            if (p.st_nt == 512) {
+            if (nt == 512) {
                 if (p.ep == KPM) return launch_staged<P, T, VT, E, KPM, 512>(p, num_cus, s);
                 if (p.ep == SERIES) return launch_staged<P, T, VT, E, SERIES, 512>(p, num_cus, s);
                 if (p.ep == PLAIN)
@@ -1507,14 +1507,53 @@ bool staged_default(const SweepParams& p) {
     return (p.ep & (EP_GTERMS | EP_GRAD)) == 0 && elems >= (int64_t(1) << 20);
 }
 
-// Elements per lane of a staged launch: one for complex128, two for
-// complex64 (one 16-byte chunk per lane and row either way; longer tiles
-// need more registers than two resident waves per SIMD allow).
+// Elements per lane of a staged launch that asks for none: one for complex128,
+// two for complex64 (one 16-byte chunk per lane and row either way).
+// staged_tile says where the built-in families take more.
 int staged_elems(const SweepParams& p) {
     static const int env_e = env_int("PV_STAGED_E", 0);
     if (p.st_E > 0) return p.st_E;
     if (env_e > 0) return env_e;
     return p.dtype == 0 ? 1 : 2;
+}
+
+// Tile of a staged launch of a built-in family that asks for no elements per
+// lane and no workgroup size.  Longer tiles re-read less x halo (two sites per
+// tile) and have more loads in flight, and pay once there are walks enough
+// for every CU: from 2^22 elements, and at 512 lanes (one workgroup per CU)
+// from 2^24 on walks of 32 planes.  us per sweep, short tile | long tile:
+//   TI c128 64^3 nb 8 (2^23)         step 88.5 | 77.2   plain 60.6 | 55.1
+//   TI c128 240x240x6 nb 32          step 548  | 533    plain 465  | 408  (512 lanes: 432)
+//   TI c128 256x256x64 nb 4          step 652  | 605    plain 514  | 446  (256 lanes: 473)
+//   TI c128 96x96x6 nb 8 (2^20.8)    step 30.0 | 32.4   plain 20.5 | 22.1: short
+//   TI c64 256x256x64 nb 4           step 352  | 293    plain 267  | 232
+//   TI c64 96x96x6 nb 32             step 49.9 | 47.8   plain 32.8 | 34.0: short walks
+//   Weyl c128 128x100x50 nb 8        step 125  | 106    plain 85.8 | 77.8
+//   graphene 512x512 c128 nb 32      step 330  | 276    plain 222  | 186   series 482 | 474
+// Series steps carry two more streams: at twice the registers per lane they
+// lose (TI c128 64^3 nb 8 113 | 129); with 512 lanes complex64 gains on long
+// walks (256x256x64 nb 4: 563 | 518) and complex128 does not (nb 8: 2122 | 2163).
+struct StagedTile {
+    int e, nt;
+};
+template <class P, typename T>
+StagedTile staged_tile(const SweepParams& p) {
+    static const int env_e = env_int("PV_STAGED_E", 0);
+    const int e0 = staged_elems(p);
+    const StagedTile t0{e0, p.st_nt == 512 ? 512 : kBlock};
+    if (P::FAMILY == FAM_GENERIC || p.st_E > 0 || p.st_nt > 0 || env_e > 0 || p.colp != nullptr) return t0;
+    const int64_t n = p.L[0] * p.L[1] * p.L[2] * P::NO * p.nb;
+    const bool series = p.ep == (EP_STORE_Y | EP_ACC_ADD), step = p.ep == (EP_STORE_Y | EP_DOTS);
+    if (n < (int64_t(1) << 22) || !(series || step || p.ep == EP_STORE_Y)) return t0;
+    if (P::DIM == 2) return {2 * e0, 512};
+    const bool c128 = sizeof(T) == 8, walks = n >= (int64_t(1) << 24) && p.L[2] >= 32;
+    if (P::FAMILY == FAM_TI) {
+        if (series) return {e0, walks && !c128 ? 512 : kBlock};
+        if (c128) return {2 * e0, walks ? 512 : kBlock};
+        return step || p.L[2] >= 32 || n >= (int64_t(1) << 25) ? StagedTile{2 * e0, kBlock} : t0;
+    }
+    if (series) return t0;
+    return c128 || (step && n >= (int64_t(1) << 23)) ? StagedTile{2 * e0, kBlock} : t0;
 }
 
 template <class X>
@@ -1541,15 +1580,15 @@ hipError_t launch_typed(SweepParams& p, int num_cus, hipStream_t s) {
         // n_orb * nb = 1 is half a chunk per site: direct kernel)
         const bool whole = (P::NO * p.nb * int(sizeof(cplx<T>))) % 16 == 0;
         if (can && aligned && whole && P::NO * p.nb <= STAGED_MAX_SITE && (kind == 2 || (kind == 0 && dflt))) {
-            const int e = staged_elems(p);
-            auto staged = [&](auto pt) -> hipError_t {
+            const auto [e, nt] = staged_tile<P, T>(p);
+            auto staged = [&, e = e, nt = nt](auto pt) -> hipError_t {
                 using Q = typename decltype(pt)::type;
                 if constexpr (sizeof(T) == 8)
-                    return e == 2 ? launch_staged_ep<Q, T, VT, 2>(p, num_cus, s)
-                                  : launch_staged_ep<Q, T, VT, 1>(p, num_cus, s);
+                    return e == 2 ? launch_staged_ep<Q, T, VT, 2>(p, nt, num_cus, s)
+                                  : launch_staged_ep<Q, T, VT, 1>(p, nt, num_cus, s);
                 else
-                    return e == 4 ? launch_staged_ep<Q, T, VT, 4>(p, num_cus, s)
-                                  : launch_staged_ep<Q, T, VT, 2>(p, num_cus, s);
+                    return e == 4 ? launch_staged_ep<Q, T, VT, 4>(p, nt, num_cus, s)
+                                  : launch_staged_ep<Q, T, VT, 2>(p, nt, num_cus, s);
             };
             if constexpr (P::FAMILY == FAM_GENERIC) {
                 if (p.generic_side_halo) return staged(Tag<PatGeneric<P::NO, true>>{});
