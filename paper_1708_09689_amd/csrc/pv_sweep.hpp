@@ -32,6 +32,7 @@
 #include "pv_kernels.hpp"
 
 #ifndef PV_RTC
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -131,6 +132,7 @@ struct KArgs {
     // the outer dimension w; m is the middle dimension (y in 3D, none in 2D)
     int st_site, st_seg, st_nxs;   // elements per site, ring row length, column tiles per row
     int st_Lm, st_Lw, st_pm, st_pw;
+    int st_rm, st_rw, st_ywalk;    // rows from one m (w) to the next; 1: w is y and m is z
     int st_C, st_Bm, st_parts;     // planes per walk, strip height, 8 XCD parts or 1
 };
 
@@ -708,6 +710,16 @@ struct StagedSide {
     u32x4 acc[S::TCH];
 };
 
+// Stencils whose rows differ along one axis at a time: the kernel can walk along
+// z with side rows y -+ 1, or along y with side rows z -+ 1.
+template <class P>
+__host__ __device__ constexpr bool walks_either() {
+    if (P::FAMILY != FAM_TI && P::FAMILY != FAM_WEYL) return false;
+    for (int t = 0; t < P::NT; ++t)
+        if ((P::off[t][0] != 0) + (P::off[t][1] != 0) + (P::off[t][2] != 0) != 1) return false;
+    return true;
+}
+
 // ZL: the step reads z (every epilogue but the plain sweep with gamma = 0)
 template <class P, typename T, typename VT, int E, bool ACC, int NT, int W, bool ZL = true>
 struct StagedCtx {
@@ -733,7 +745,7 @@ struct StagedCtx {
     int vshift = 0;  // element -> field entry: log2 of elements per site or per orbital row
 
     __device__ __forceinline__ int64_t row_of(int mm, int ww) const {
-        return P::DIM == 3 ? (int64_t)ww * a.Ly + mm : (int64_t)ww;
+        return P::DIM == 3 ? (int64_t)ww * a.st_rw + (int64_t)mm * a.st_rm : (int64_t)ww;
     }
     // Row (mm, ww) after wrapping periodic dimensions; -1 when an open
     // boundary drops it.  Integer selects (no boolean state across blocks),
@@ -866,11 +878,14 @@ struct StagedCtx {
             for (int k = 0; k < EL; ++k) vl[tid + k * S::NTH] = T(st.v[k]);
         }
     }
-    // Ring row (m, ww) alone into a slot (walk prologue).
-    __device__ __forceinline__ void ring_now(u32x4 (&r)[S::RCH], int ww, int slot) const {
+    // Ring row (m, ww) alone, and its hand-over to a slot (start of a walk: all
+    // of its loads are in flight before the first wait).
+    __device__ __forceinline__ void ring_load(u32x4 (&r)[S::RCH], int ww) const {
         const cplx<T>* rp = row_ptr(m, ww);
 #pragma unroll
         for (int k = 0; k < S::RCH; ++k) r[k] = ld_chunk<T>(rp, roff[k]);
+    }
+    __device__ __forceinline__ void ring_store(const u32x4 (&r)[S::RCH], int slot) const {
         u32x4* d = reinterpret_cast<u32x4*>(ring + slot * a.st_seg);
 #pragma unroll
         for (int k = 0; k < S::RCH; ++k) d[tid + k * S::NTH] = r[k];
@@ -1050,10 +1065,15 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
         // wa + 2 and the rows of step 1, left in flight
         Set A, B;
         typename Ctx::Side SD;
-        cx.ring_now(A.ring, wa - 1, 0);
-        cx.ring_now(B.ring, wa, 1);
-        cx.issue_side(SD, wa);
-        cx.issue(A, wa + 1, wa);
+        {
+            u32x4 r0[S::RCH], r1[S::RCH];
+            cx.ring_load(r0, wa - 1);
+            cx.ring_load(r1, wa);
+            cx.issue_side(SD, wa);
+            cx.issue(A, wa + 1, wa);
+            cx.ring_store(r0, 0);
+            cx.ring_store(r1, 1);
+        }
         cx.commit(A, 2);
         cx.commit_side(SD);
         El zc[EL], ac[EL];   // z and acc of the step at hand (ZR)
@@ -1082,6 +1102,11 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
             const El* rm = cx.ring + (s % 3) * a.st_seg + site;
             const El* r0 = cx.ring + ((s + 1) % 3) * a.st_seg + site;
             const El* rp = cx.ring + ((s + 2) % 3) * a.st_seg + site;
+            // the rows y -+ 1 and z -+ 1 of a stencil that walks along either axis
+            const El* ylo = a.st_ywalk ? rm : cx.tra;
+            const El* yhi = a.st_ywalk ? rp : cx.tra + Ctx::Side::SLEN;
+            const El* zlo = a.st_ywalk ? cx.tra : rm;
+            const El* zhi = a.st_ywalk ? cx.tra + Ctx::Side::SLEN : rp;
             const int64_t rowi = cx.row_of(cx.m, w);
             const int64_t rb = rowi * a.rowel;
             El hv[EL], xs_[EL], zv[EL], av[EL];
@@ -1136,6 +1161,11 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
                         constexpr int dx = t < P::NT ? P::off[tt][0] : 0;
                         if constexpr (t == P::NT) {
                             v = r0[l + dqj];
+                        } else if constexpr (walks_either<P>()) {
+                            constexpr int dy = P::off[tt][1], dz = P::off[tt][2];
+                            if constexpr (dx != 0) v = r0[l + dx * site + dqj];
+                            else if constexpr (dy != 0) v = (dy < 0 ? ylo : yhi)[l + dqj];
+                            else v = (dz < 0 ? zlo : zhi)[l + dqj];
                         } else {
                             constexpr int dm = P::DIM == 3 ? P::off[tt][1] : 0;
                             constexpr int dw = P::DIM == 3 ? P::off[tt][2] : P::off[tt][1];
@@ -1371,35 +1401,81 @@ size_t staged_lds_bytes() {
     return staged_lds_bytes_for<P, T, E, NT, W>(EPM == 0u || (EPM & EP_ACC_ADD) != 0u);
 }
 
+// Walks of a staged launch: which axis they follow and how many planes each.
+// One eighth of the lattice (the largest XCD part, split along m when there are
+// 8 middle rows, else along w) is nm rows m by nW planes; in nwc chunks of C
+// planes it is `items` walks over G8 workgroups.  A walk costs its planes and
+// about two more to fill the ring, and a last round of walks that leaves
+// workgroups idle costs about three tenths of what it would if they did not
+// leave their bandwidth to the others.
+struct StagedWalk {
+    int nm = 0, nW = 0, C = 1, items = 1;
+    double cost = 0.0;
+    StagedWalk(int Lm, int Lw, int nxs) {
+        const bool split_m = Lm >= 8;
+        nm = split_m ? (Lm + 7) / 8 : Lm;
+        nW = split_m ? Lw : (Lw + 7) / 8;
+        chunk(nW, nxs, 1);
+    }
+    void chunk(int planes, int nxs, int G8) {
+        C = planes < nW ? planes : nW;
+        if (C < 1) C = 1;
+        items = nW < 1 ? 1 : ((nW + C - 1) / C) * nm * nxs;
+        const int rounds = (items + G8 - 1) / G8;
+        cost = (0.7 * std::max(1.0, double(items) / G8) + 0.3 * rounds) * (C + 2);
+    }
+};
+
+// The walks of a launch that asks for none: along w in as few chunks as give
+// every workgroup one, or, where that costs 8% less, in up to 8 chunks that
+// fill the last round, or (built-in 3D stencils, fewer than 8 planes z) along
+// y.  us per sweep, before | after:
+//   TI c128 240x240x6 nb 32   step 522 | 447   plain 402 | 346   series 790 | 703   (along y)
+//   TI c128 240x240x6 nb 2    step 37.6 | 33.6   plain 30.1 | 27.4   series 50.2 | 45.6   (along y)
+//   TI c64 57x83x46 nb 8      step 56.8 | 43.0   plain 45.3 | 33.3   series 66.3 | 62.1   (5, 5, 2 chunks)
+// Along y with 8 planes or more the parts are single rows m, whose side rows
+// other XCDs load: 96x96x8 nb 16 step 54.0 | 58.0 at best.
 template <class P, typename T, typename VT, int E, int NT, int W>
 int staged_setup(const SweepParams& p, int G8, bool full_walk, KArgs<T, VT>& a) {
     constexpr int TW = NT * E;   // complex numbers of a column tile
     a.st_site = P::NO * p.nb;
     a.st_seg = staged_seg<T, E, NT, W>();   // ring slot; its first elements hold the tile and two sites
     a.st_nxs = (a.rowel + TW - 1) / TW;
-    if (P::DIM == 3) {
-        a.st_Lm = a.Ly; a.st_Lw = a.Lz; a.st_pm = a.py; a.st_pw = a.pz;
+    a.st_ywalk = 0;
+    StagedWalk k(P::DIM == 3 ? a.Ly : 1, P::DIM == 3 ? a.Lz : a.Ly, a.st_nxs);
+    if (p.st_C > 0 || full_walk) {
+        k.chunk(full_walk && p.st_C <= 0 ? k.nW : p.st_C, a.st_nxs, 1);
     } else {
+        auto fill = [&](const StagedWalk& from, StagedWalk& best, int ywalk) {
+            for (int nwc = 1; nwc <= 8; ++nwc) {
+                StagedWalk t = from;
+                t.chunk((t.nW + nwc - 1) / nwc, a.st_nxs, G8);
+                if (t.cost >= best.cost) continue;
+                best = t;
+                a.st_ywalk = ywalk;
+            }
+        };
+        const int cols = k.nm * a.st_nxs, n0 = std::max(1, std::min((G8 + cols - 1) / cols, k.nW));
+        k.chunk((k.nW + n0 - 1) / n0, a.st_nxs, G8);
+        if (p.st_Bm <= 0 && p.st_G8 <= 0) {
+            const StagedWalk k0 = k;
+            k.cost *= 0.92;
+            fill(k0, k, 0);
+            if (walks_either<P>() && a.Lz < 8) fill(StagedWalk(a.Lz, a.Ly, a.st_nxs), k, 1);
+        }
+    }
+    a.st_C = k.C;
+    if (P::DIM != 3) {
         a.st_Lm = 1; a.st_Lw = a.Ly; a.st_pm = 0; a.st_pw = a.py;
-    }
-    // the largest part: a split along m when there are 8 middle rows, else along w
-    const bool split_m = a.st_Lm >= 8;
-    const int nm = split_m ? (a.st_Lm + 7) / 8 : a.st_Lm;
-    const int nW = split_m ? a.st_Lw : (a.st_Lw + 7) / 8;
-    const int cols = nm * a.st_nxs;
-    if (nW < 1) {
-        a.st_C = 1;
-    } else if (p.st_C > 0) {
-        a.st_C = p.st_C < nW ? p.st_C : nW;
-    } else if (full_walk) {
-        a.st_C = nW;
+        a.st_rm = 0; a.st_rw = 1;
+    } else if (a.st_ywalk) {
+        a.st_Lm = a.Lz; a.st_Lw = a.Ly; a.st_pm = a.pz; a.st_pw = a.py;
+        a.st_rm = a.Ly; a.st_rw = 1;
     } else {
-        int nwc = (G8 + cols - 1) / cols;
-        if (nwc > nW) nwc = nW;
-        a.st_C = (nW + nwc - 1) / nwc;
+        a.st_Lm = a.Ly; a.st_Lw = a.Lz; a.st_pm = a.py; a.st_pw = a.pz;
+        a.st_rm = 1; a.st_rw = a.Ly;
     }
-    const int items = nW < 1 ? 1 : ((nW + a.st_C - 1) / a.st_C) * cols;
-    if (G8 > items) G8 = items;
+    if (G8 > k.items) G8 = k.items;
     int bx = int(std::lround(std::sqrt(double(G8) * a.st_site / TW)));
     if (bx > a.st_nxs) bx = a.st_nxs;
     if (bx < 1) bx = 1;
