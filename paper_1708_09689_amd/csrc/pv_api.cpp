@@ -1021,15 +1021,23 @@ pv_status kpm_forward(pv_lattice* l, int dtype, int nb, int M, double a, double 
     if ((st = fill_traversal(l, dtype, nb, p)) != PV_OK) return st;
     p.ep = pv::EP_STORE_Y | pv::EP_DOTS;
     const double invD = 1.0 / double(l->n_rows);
-    int n0 = 0, grid0 = 0;   // first step not reduced yet, rows of its partials
+    // first step not reduced yet, its buffer, rows of its partials (the steps
+    // that read r may have another launch shape: r need not be aligned)
+    int n0 = 0, buf0 = 0, grid0 = 0;
+    auto reduce_before = [&](int n) -> hipError_t {
+        const hipError_t e = pv::launch_kpm_reduce(part + buf0 * stride, stride, grid0, nb, 4, n0, n - n0, mu, M, invD, s);
+        buf0 += n - n0;
+        n0 = n;
+        return e;
+    };
     auto step_sweep = [&](int n) -> hipError_t {
-        p.partials = part + (n - n0) * stride;
-        if (hipError_t e = pv::launch_sweep(p, num_cus(), s); e != hipSuccess) return e;
-        if (n == n0) grid0 = p.grid;
-        if (p.grid != grid0) return hipErrorInvalidValue;   // one launch shape for all steps
-        if (n + 1 < M / 2 && n + 1 - n0 < buffers) return hipSuccess;
-        const hipError_t e = pv::launch_kpm_reduce(part, stride, grid0, nb, 4, n0, n + 1 - n0, mu, M, invD, s);
-        n0 = n + 1;
+        p.partials = part + (buf0 + n - n0) * stride;
+        hipError_t e = pv::launch_sweep(p, num_cus(), s);
+        if (e == hipSuccess && n > n0 && p.grid != grid0) e = reduce_before(n);
+        grid0 = p.grid;
+        if (e != hipSuccess || (n + 1 < M / 2 && buf0 + n + 1 - n0 < buffers)) return e;
+        e = reduce_before(n + 1);
+        buf0 = 0;
         return e;
     };
     // w_1 = H~ w_0

@@ -64,3 +64,21 @@ def test_pairs_of_columns_equal_single_columns(name, L, per, nb, elems, wg):
     pv.pv_cheb_series(c.lat, x, y, 9.0, 0.1, coef)
     pv.pv_cheb_series(c.lat, x, w, 9.0, 0.1, coef)
     assert np.array_equal(host(y), host(w))
+
+
+@pytest.mark.parametrize("name,L,nb", [("ti", (64, 64, 64), 1), ("ti", (64, 64, 64), 2), ("weyl", (61, 67, 70), 4),
+                                       ("graphene4", (300, 301), 16)])
+@pytest.mark.parametrize("M", [2, 4, 6, 160])
+def test_kpm_of_start_vectors_off_alignment(name, L, nb, M):
+    """The steps that read a start block 8 bytes off a 16-byte boundary take
+    another kernel, with another number of partial sums, than the others.  Both
+    runs round every number alike up to the contraction of single operations:
+    at unit norm, M steps of 24 roundings at eps = 6e-8 summed over random
+    signs, sqrt(M) * 24 * eps < 2e-5."""
+    c = Case(name, L, (1,) * len(L), seed=43, vdtype=np.float32)
+    assert c.D * nb >= 1 << 20
+    r = dev(c.block(nb, kind="phase", dtype=np.complex64))
+    a = 9.0
+    ref = host(pv.pv_kpm_moments(c.lat, r, M, a, 0.0))
+    mu = host(pv.pv_kpm_moments(c.lat, halfway(r), M, a, 0.0))
+    assert np.abs(mu - ref).max() < 2e-5
