@@ -1019,13 +1019,13 @@ pv_status kpm_forward(pv_lattice* l, int dtype, int nb, int M, double a, double 
     const int64_t stride = int64_t(partial_bytes(l, nb) / sizeof(double));
     pv::SweepParams p = base_params(l, dtype, nb);
     if ((st = fill_traversal(l, dtype, nb, p)) != PV_OK) return st;
-    p.ep = pv::EP_STORE_Y | pv::EP_DOTS;
+    p.ep = pv::EP_STORE_Y | pv::EP_MOMENTS;
     const double invD = 1.0 / double(l->n_rows);
     // first step not reduced yet, its buffer, rows of its partials (the steps
     // that read r may have another launch shape: r need not be aligned)
     int n0 = 0, buf0 = 0, grid0 = 0;
     auto reduce_before = [&](int n) -> hipError_t {
-        const hipError_t e = pv::launch_kpm_reduce(part + buf0 * stride, stride, grid0, nb, 4, n0, n - n0, mu, M, invD, s);
+        const hipError_t e = pv::launch_kpm_reduce(part + buf0 * stride, stride, grid0, nb, 2, n0, n - n0, mu, M, invD, s);
         buf0 += n - n0;
         n0 = n;
         return e;
@@ -1786,10 +1786,10 @@ extern "C" pv_status pv_autotune(pv_lattice* l, int dtype, int nb, const char* c
                 p.eta_im = 0.25;
                 if (hipError_t e = pv::launch_sweep(p, num_cus(), s); e != hipSuccess) return e;
             } else {
-                p.ep = pv::EP_STORE_Y | pv::EP_DOTS;
+                p.ep = pv::EP_STORE_Y | pv::EP_MOMENTS;
                 p.partials = part;
                 hipError_t e = pv::launch_sweep(p, num_cus(), s);
-                if (e == hipSuccess) e = pv::launch_reduce_dots(part, p.grid, nb, dots, s);
+                if (e == hipSuccess) e = pv::launch_kpm_reduce(part, 0, p.grid, nb, 2, 0, 1, dots, 2, 1.0, s);
                 if (e != hipSuccess) return e;
             }
         }
@@ -2732,7 +2732,7 @@ extern "C" pv_status pv_batch_kpm_moments(pv_batch* B, int dtype, int nb, int M,
             // variants 0 and 2 run even steps, 1 and 3 odd ones; dots into the
             // launch's buffer
             p.partials = reinterpret_cast<double*>(w + L.partials);
-            p.ep = pv::EP_STORE_Y | pv::EP_DOTS;
+            p.ep = pv::EP_STORE_Y | pv::EP_MOMENTS;
             p.beta = b[i];
             if (v == 0) {          // w_1 = H~ w_0
                 p.x = r[i]; p.y = A; p.z = nullptr; p.alpha = 1.0 / a[i]; p.gamma = 0.0;
@@ -2767,7 +2767,7 @@ extern "C" pv_status pv_batch_kpm_moments(pv_batch* B, int dtype, int nb, int M,
             return fail(PV_ERR_UNSUPPORTED, "all instances of a batch need the same field type");
     pv::SweepParams p0 = batch_params(B, 0, dtype, nb);
     p0.vtype = vtype;
-    p0.ep = pv::EP_STORE_Y | pv::EP_DOTS;
+    p0.ep = pv::EP_STORE_Y | pv::EP_MOMENTS;
     // a generated kernel is compiled and loaded before the capture
     if (p0.cg_src) PV_HIP(pv::codegen_prepare_batch(p0, L.staged));
     PV_HIP(hipStreamBeginCapture(B->cap, hipStreamCaptureModeRelaxed));

@@ -278,7 +278,7 @@ hipError_t staged_go(SweepParams& p, int num_cus, hipStream_t s, unsigned epm) {
 // time (complex128: one element per lane).
 template <class P, typename T, typename VT, int E>
 hipError_t staged_ep(SweepParams& p, int num_cus, hipStream_t s) {
-    constexpr unsigned KPM = EP_STORE_Y | EP_DOTS, SERIES = EP_STORE_Y | EP_ACC_ADD, PLAIN = EP_STORE_Y;
+    constexpr unsigned KPM = EP_STORE_Y | EP_MOMENTS, DOTS = EP_STORE_Y | EP_DOTS, SERIES = EP_STORE_Y | EP_ACC_ADD, PLAIN = EP_STORE_Y;
     constexpr int E0 = sizeof(T) == 8 ? 1 : 2;
     if constexpr (E != E0) {
         // a tile whose rows (six side rows with SIDE_W) overflow the CU's LDS
@@ -289,7 +289,7 @@ hipError_t staged_ep(SweepParams& p, int num_cus, hipStream_t s) {
     }
     if (p.colp == nullptr) {
         unsigned epm = 0u;
-        if (p.ep == KPM) epm = KPM;
+        if (p.ep == KPM || p.ep == DOTS) epm = p.ep;
         else if (p.ep == SERIES) epm = SERIES;
         else if (p.ep == PLAIN) epm = p.gamma == 0.0 ? (PLAIN | EP_NO_Z) : PLAIN;
         if (epm != 0u) {
@@ -441,7 +441,7 @@ hipError_t batch_function(const SweepParams& p, int staged, bool nocompile, Comp
         return batch_tile<P, T>(p, [&](auto ke, auto kn, auto kw) -> hipError_t {
             constexpr int E = decltype(ke)::value, NT = decltype(kn)::value, W = decltype(kw)::value;
             std::snprintf(expr, sizeof expr, "&pv::batch_staged_kernel<pv::PatCG, %s, %s, %d, %uu, %d, %d>", tname<T>(),
-                          tname<VT>(), E, unsigned(EP_STORE_Y | EP_DOTS), NT, W);
+                          tname<VT>(), E, unsigned(EP_STORE_Y | EP_MOMENTS), NT, W);
             nt = NT;
             lds = staged_lds_bytes_for<P, T, E, NT, W>(false);
             return function_for(p.cg_src, expr, NT, lds, nocompile, c);
@@ -462,7 +462,7 @@ hipError_t codegen_prepare_batch(const SweepParams& p, int staged) {
 hipError_t launch_batch_codegen(const SweepParams& p, int staged, const void* table, const int* block_inst,
                                 const int* inst_block0, int grid, int64_t part_off, hipStream_t s) {
     g_err.clear();
-    if (staged && p.ep != (EP_STORE_Y | EP_DOTS)) return hipErrorInvalidValue;
+    if (staged && p.ep != (EP_STORE_Y | EP_MOMENTS)) return hipErrorInvalidValue;
     Compiled c;
     int nt = 0;
     size_t lds = 0;

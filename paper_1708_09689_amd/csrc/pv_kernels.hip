@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kBlock) void batch_reduce_kernel(const double* __re
                                                               const double* __restrict__ invD) {
     const int i = blockIdx.x / nb, c = blockIdx.x % nb;
     const int b0 = inst_block0[i], b1 = inst_block0[i + 1];
-    kpm_reduce(partials + (size_t)b0 * nb * 4, stride, b1 - b0, nb, 4, c, n0, blockIdx.y, mu + (size_t)blockIdx.x * M,
+    kpm_reduce(partials + (size_t)b0 * nb * 2, stride, b1 - b0, nb, 2, c, n0, blockIdx.y, mu + (size_t)blockIdx.x * M,
                invD[i]);
 }
 

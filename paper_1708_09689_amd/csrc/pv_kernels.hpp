@@ -44,6 +44,7 @@ enum : unsigned {
     EP_ACC_INIT = 2u,    // acc_out = eta0 * x + eta * y
     EP_ACC_ADD = 4u,     // acc_out = acc_in + eta * y
     EP_DOTS = 8u,        // per-block partial dots (xx, Re xy, Im xy, yy)
+    EP_MOMENTS = 128u,   // per-block partial dots (xx, Re xy): what KPM moments take
     EP_GTERMS = 16u,     // y += sum_j gcoef[j][c] gw_j (adjoint source terms)
     EP_GRAD = 32u,       // grad += gx Re(conj(x) gw_1) + gy Re(conj(y) gw_0) per site/row
     EP_NO_Z = 64u,       // launch-internal: gamma = 0, z is neither loaded nor staged
@@ -93,7 +94,7 @@ struct SweepParams {
     double alpha, beta, gamma;
     double eta_re, eta_im, eta0_re, eta0_im;
     unsigned ep;
-    double* partials;     // [grid][nb][4] when EP_DOTS
+    double* partials;     // [grid][nb][4] when EP_DOTS, [grid][nb][2] when EP_MOMENTS
     int grid;             // set by launch_sweep: number of workgroups
     // generated kernels (generic stencils): source of the stencil's pattern
     // struct pv::PatCG, NULL for the interpreted generic kernels; its

@@ -290,13 +290,15 @@ __device__ __forceinline__ void epilogue_ep(const KArgs<T, VT>& a, const unsigne
     } else if (ep & EP_ACC_ADD) {
         st_nt(a.acc_out + e, av.re + er * yr - ei * yi, av.im + er * yi + ei * yr);
     }
-    if (ep & EP_DOTS) {
+    if (ep & (EP_DOTS | EP_MOMENTS)) {
         const double xr = double(xc.re), xi = double(xc.im);
         const double dyr = double(yr), dyi = double(yi);
         dxx += xr * xr + xi * xi;
         dxr += xr * dyr + xi * dyi;
-        dxi += xr * dyi - xi * dyr;
-        dyy += dyr * dyr + dyi * dyi;
+        if (ep & EP_DOTS) {
+            dxi += xr * dyi - xi * dyr;
+            dyy += dyr * dyr + dyi * dyi;
+        }
     }
     if (ep & EP_GRAD) {
         double g = a.gx * (double(xc.re) * double(gv[1].re) + double(xc.im) * double(gv[1].im)) +
@@ -546,13 +548,18 @@ __device__ __forceinline__ void sweep_block(const KArgs<T, VT>& a, int b_out, in
                  dxi, dyy);
     }
 
-    if (a.ep & EP_DOTS) {
+    if (a.ep & (EP_DOTS | EP_MOMENTS)) {
         // lanes with the same column: lane = (site * NO + o) * nb + c inside the wave
+        const int ndot = (a.ep & EP_DOTS) ? 4 : 2;
         for (int m = nb; m < 64; m <<= 1) {
             dxx += __shfl_xor(dxx, m);
             dxr += __shfl_xor(dxr, m);
-            dxi += __shfl_xor(dxi, m);
-            dyy += __shfl_xor(dyy, m);
+        }
+        if (ndot == 4) {
+            for (int m = nb; m < 64; m <<= 1) {
+                dxi += __shfl_xor(dxi, m);
+                dyy += __shfl_xor(dyy, m);
+            }
         }
         __shared__ double red[kBlock / 64][PV_MAX_NB_K][4];
         const int wave = tid >> 6, lane = tid & 63;
@@ -563,11 +570,11 @@ __device__ __forceinline__ void sweep_block(const KArgs<T, VT>& a, int b_out, in
             red[wave][lane][3] = dyy;
         }
         __syncthreads();
-        if (tid < nb * 4) {
-            const int cc = tid >> 2, k = tid & 3;
+        if (tid < nb * ndot) {
+            const int cc = ndot == 4 ? tid >> 2 : tid >> 1, k = tid & (ndot - 1);
             double sum = 0.0;
             for (int w = 0; w < kBlock / 64; ++w) sum += red[w][cc][k];
-            a.partials[((size_t)b_out * nb + cc) * 4 + k] = sum;
+            a.partials[((size_t)b_out * nb + cc) * ndot + k] = sum;
         }
     }
 }
@@ -944,13 +951,15 @@ __device__ __forceinline__ void staged_epilogue(const KArgs<T, VT>& a, int64_t e
             ao[2 * q] = acc.v[q].re + er * yr - ei * yi;
             ao[2 * q + 1] = acc.v[q].im + er * yi + ei * yr;
         }
-        if constexpr ((EPM & EP_DOTS) != 0u) {
+        if constexpr ((EPM & (EP_DOTS | EP_MOMENTS)) != 0u) {
             const double xr = double(x.v[q].re), xi = double(x.v[q].im);
             const double dyr = double(yr), dyi = double(yi);
             dxx[q] += xr * xr + xi * xi;
             dxr[q] += xr * dyr + xi * dyi;
-            dxi[q] += xr * dyi - xi * dyr;
-            dyy[q] += dyr * dyr + dyi * dyi;
+            if constexpr ((EPM & EP_DOTS) != 0u) {
+                dxi[q] += xr * dyi - xi * dyr;
+                dyy[q] += dyr * dyr + dyi * dyi;
+            }
         }
     }
     if constexpr ((EPM & EP_STORE_Y) != 0u) __builtin_nontemporal_store(yo, reinterpret_cast<V*>(a.y + e));
@@ -1229,14 +1238,17 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
         if (s < nsteps) step(s, A, B);
     }
 
-    if (ep & EP_DOTS) {
+    if (ep & (EP_DOTS | EP_MOMENTS)) {
+        const int ndot = (ep & EP_DOTS) ? 4 : 2;
 #pragma unroll
         for (int q = 0; q < W; ++q)
             for (int mm = nb; mm < 64; mm <<= 1) {
                 dxx[q] += __shfl_xor(dxx[q], mm);
                 dxr[q] += __shfl_xor(dxr[q], mm);
-                dxi[q] += __shfl_xor(dxi[q], mm);
-                dyy[q] += __shfl_xor(dyy[q], mm);
+                if (ndot == 4) {
+                    dxi[q] += __shfl_xor(dxi[q], mm);
+                    dyy[q] += __shfl_xor(dyy[q], mm);
+                }
             }
         __syncthreads();
         double* red = reinterpret_cast<double*>(smem);   // the ring is free after the last barrier
@@ -1252,11 +1264,11 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
             }
         }
         __syncthreads();
-        if (tid < a.nb * 4) {
-            const int cc = tid >> 2, q = tid & 3;
+        if (tid < a.nb * ndot) {
+            const int cc = ndot == 4 ? tid >> 2 : tid >> 1, q = tid & (ndot - 1);
             double sum = 0.0;
             for (int wv = 0; wv < NT / 64; ++wv) sum += red[(wv * PV_MAX_NB_K + cc) * 4 + q];
-            a.partials[((size_t)b_out * a.nb + cc) * 4 + q] = sum;
+            a.partials[((size_t)b_out * a.nb + cc) * ndot + q] = sum;
         }
     }
 }
@@ -1542,11 +1554,13 @@ hipError_t launch_staged(SweepParams& p, int num_cus, hipStream_t s) {
 // every other combination with the flags read at run time.
 template <class P, typename T, typename VT, int E>
 hipError_t launch_staged_ep(SweepParams& p, int nt, int num_cus, hipStream_t s) {
-    constexpr unsigned KPM = EP_STORE_Y | EP_DOTS, SERIES = EP_STORE_Y | EP_ACC_ADD, PLAIN = EP_STORE_Y;
+    constexpr unsigned KPM = EP_STORE_Y | EP_MOMENTS, DOTS = EP_STORE_Y | EP_DOTS, SERIES = EP_STORE_Y | EP_ACC_ADD,
+                       PLAIN = EP_STORE_Y;
     if (p.colp == nullptr) {
         if constexpr (P::FAMILY != FAM_GENERIC) {
             if (nt == 512) {
                 if (p.ep == KPM) return launch_staged<P, T, VT, E, KPM, 512>(p, num_cus, s);
+                if (p.ep == DOTS) return launch_staged<P, T, VT, E, DOTS, 512>(p, num_cus, s);
                 if (p.ep == SERIES) return launch_staged<P, T, VT, E, SERIES, 512>(p, num_cus, s);
                 if (p.ep == PLAIN)
                     return p.gamma == 0.0 ? launch_staged<P, T, VT, E, PLAIN | EP_NO_Z, 512>(p, num_cus, s)
@@ -1554,6 +1568,7 @@ hipError_t launch_staged_ep(SweepParams& p, int nt, int num_cus, hipStream_t s) 
             }
         }
         if (p.ep == KPM) return launch_staged<P, T, VT, E, KPM>(p, num_cus, s);
+        if (p.ep == DOTS) return launch_staged<P, T, VT, E, DOTS>(p, num_cus, s);
         if (p.ep == SERIES) return launch_staged<P, T, VT, E, SERIES>(p, num_cus, s);
         if (p.ep == PLAIN)
             return p.gamma == 0.0 ? launch_staged<P, T, VT, E, PLAIN | EP_NO_Z>(p, num_cus, s)
@@ -1619,7 +1634,7 @@ StagedTile staged_tile(const SweepParams& p) {
     const StagedTile t0{e0, p.st_nt == 512 ? 512 : kBlock};
     if (P::FAMILY == FAM_GENERIC || p.st_E > 0 || p.st_nt > 0 || env_e > 0 || p.colp != nullptr) return t0;
     const int64_t n = p.L[0] * p.L[1] * p.L[2] * P::NO * p.nb;
-    const bool series = p.ep == (EP_STORE_Y | EP_ACC_ADD), step = p.ep == (EP_STORE_Y | EP_DOTS);
+    const bool series = p.ep == (EP_STORE_Y | EP_ACC_ADD), step = p.ep == (EP_STORE_Y | EP_DOTS) || p.ep == (EP_STORE_Y | EP_MOMENTS);
     if (n < (int64_t(1) << 22) || !(series || step || p.ep == EP_STORE_Y)) return t0;
     if (P::DIM == 2) return {2 * e0, 512};
     const bool c128 = sizeof(T) == 8, walks = n >= (int64_t(1) << 24) && p.L[2] >= 32;
@@ -1765,7 +1780,7 @@ hipError_t launch_batch_sweep_fam(const SweepParams& p, int staged, const void* 
         using VT = typename decltype(tv)::type;
         if constexpr (P::FAMILY != FAM_GENERIC) {
             if (staged) {
-                constexpr unsigned KPM = EP_STORE_Y | EP_DOTS;
+                constexpr unsigned KPM = EP_STORE_Y | EP_MOMENTS;
                 if (p.ep != KPM) return hipErrorInvalidValue;
                 hipError_t e = hipSuccess;
                 batch_shape<T>(p, [&](auto ke, auto kn, auto kw) {
