@@ -381,7 +381,9 @@ def bench_chebtp_graphene(pv, torch, W, dev, steps=5):
     pv.pv_cheb_propagate(lat, psi, 3.06, 0.05, -10.0, 64, 200)
     back = float((torch.linalg.vector_norm(psi - psi0) / torch.linalg.vector_norm(psi0)).item())
     lups = lat.n_rows * 64
-    by = lat.n_rows * (4 * 16) + lat.n_sites * 8   # x, z, acc in/out (+y) per sweep, field
+    # per step: a pass of six steps reads two vectors, acc and the field and
+    # writes two vectors and acc
+    by = (lat.n_rows * 16 * 6 + lat.n_sites * 8) / 6
     return {"workload": "graphene 1024x1024 cells x 2 sites, open x / periodic y, dot array, packet; "
                         f"runs of {steps} time steps of dt=10 (median of 3), M=64, complex128",
             "ms_per_time_step": round(ms, 4), "GLUP/s": round(lups / (ms * 1e-3) / 1e9, 3),
@@ -401,10 +403,14 @@ def bench_filter(pv, torch, lat, dev, nb=32, K=8):
     coef = np.linspace(1.0, 0.1, K + 1)
     pv.pv_cheb_series(lat, X, Y, A_SCALE, B_SHIFT, coef)
     ms = _median_timed(torch, lambda: pv.pv_cheb_series(lat, X, Y, A_SCALE, B_SHIFT, coef), 2) / K
-    by = lat.n_rows * nb * 16 * 5 + lat.n_sites * 8
+    # x, z read and y written (not z at k = 1, not y at k = K), and the
+    # accumulator read and written every third step and at k = K
+    acc = sum(2 for k in range(1, K + 1) if k == K or k % 3 == 2) - 1   # the first one is not read
+    streams = (3 * K - 2 + acc) / K
+    by = lat.n_rows * nb * 16 * streams + lat.n_sites * 8
     return {"workload": f"TI 256x256x64, nb={nb}, complex128, series of degree {K} (filter step)",
             "ms_per_sweep": round(ms, 4), "GLUP/s": round(lat.n_rows * nb / (ms * 1e-3) / 1e9, 3),
-            "GB/s": round(by / (ms * 1e-3) / 1e9, 1), "bytes_per_LUP": 80}
+            "GB/s": round(by / (ms * 1e-3) / 1e9, 1), "bytes_per_LUP": round(16 * streams, 1)}
 
 
 def bench_plain(pv, torch, lat, dev):

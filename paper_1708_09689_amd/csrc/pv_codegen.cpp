@@ -278,7 +278,7 @@ hipError_t staged_go(SweepParams& p, int num_cus, hipStream_t s, unsigned epm) {
 // time (complex128: one element per lane).
 template <class P, typename T, typename VT, int E>
 hipError_t staged_ep(SweepParams& p, int num_cus, hipStream_t s) {
-    constexpr unsigned KPM = EP_STORE_Y | EP_MOMENTS, DOTS = EP_STORE_Y | EP_DOTS, SERIES = EP_STORE_Y | EP_ACC_ADD, PLAIN = EP_STORE_Y;
+    constexpr unsigned KPM = EP_STORE_Y | EP_MOMENTS, DOTS = EP_STORE_Y | EP_DOTS, SERIES = EP_SERIES, PLAIN = EP_STORE_Y;
     constexpr int E0 = sizeof(T) == 8 ? 1 : 2;
     if constexpr (E != E0) {
         // a tile whose rows (six side rows with SIDE_W) overflow the CU's LDS

@@ -41,8 +41,11 @@ enum : unsigned char { CZ = 0, CR = 1, CI = 2, CC = 3 };
 // Epilogue flags of a sweep.
 enum : unsigned {
     EP_STORE_Y = 1u,     // write y
-    EP_ACC_INIT = 2u,    // acc_out = eta0 * x + eta * y
-    EP_ACC_ADD = 4u,     // acc_out = acc_in + eta * y
+    EP_ACC_INIT = 2u,    // acc_out = [etaz * z] + [etax * x] + eta * y
+    EP_ACC_ADD = 4u,     // acc_out = acc_in + [etaz * z] + [etax * x] + eta * y
+    EP_ACC_X = 256u,     // the accumulated sum has the term of x,
+    EP_ACC_Z = 512u,     // and of z
+    EP_SERIES = 1u | 4u | 256u | 512u,   // the accumulating step of a long series
     EP_DOTS = 8u,        // per-block partial dots (xx, Re xy, Im xy, yy)
     EP_MOMENTS = 128u,   // per-block partial dots (xx, Re xy): what KPM moments take
     EP_GTERMS = 16u,     // y += sum_j gcoef[j][c] gw_j (adjoint source terms)
@@ -92,7 +95,7 @@ struct SweepParams {
     // the fields above
     int acc_kernel, acc_E, acc_C, acc_Bm, acc_G8, acc_nt;
     double alpha, beta, gamma;
-    double eta_re, eta_im, eta0_re, eta0_im;
+    double eta_re, eta_im, etax_re, etax_im, etaz_re, etaz_im;
     unsigned ep;
     double* partials;     // [grid][nb][4] when EP_DOTS, [grid][nb][2] when EP_MOMENTS
     int grid;             // set by launch_sweep: number of workgroups

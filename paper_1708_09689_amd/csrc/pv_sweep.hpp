@@ -10,7 +10,7 @@
 //     y = alpha (H x - beta x) + gamma z
 // where H acts matrix-free through the stencil blocks of the lattice
 // (Sec. 3.2 DSL: one block per neighbour offset), and optionally
-//     acc = eta0 x + eta y   or   acc += eta y     (Chebyshev series, Sec. 4)
+//     acc = etaz z + etax x + eta y   or   acc += ...   (Chebyshev series, Sec. 4)
 //     partial sums of <x,x>, <x,y>, <y,y>           (fused dots, Sec. 3.2/3.5)
 //
 // Work decomposition: one lane owns one element (site s, orbital row o,
@@ -126,7 +126,7 @@ struct KArgs {
     int nb, lognb, logsite;
     int n_terms, pot_mode;
     double alpha, beta, gamma;
-    double eta_re, eta_im, eta0_re, eta0_im;
+    double eta_re, eta_im, etax_re, etax_im, etaz_re, etaz_im;
     unsigned ep;
     // staged traversal (staged_kernel): column tiles of one row walked along
     // the outer dimension w; m is the middle dimension (y in 3D, none in 2D)
@@ -249,6 +249,13 @@ __device__ __forceinline__ cplx<T> ld_row_nt(const cplx<T>* row, uint32_t boff) 
     return ld_nt(reinterpret_cast<const cplx<T>*>(reinterpret_cast<const char*>(row) + boff));
 }
 
+// acc += eta v
+template <typename T>
+__device__ __forceinline__ void add_term(T& ar, T& ai, T er, T ei, T vr, T vi) {
+    ar = ar + er * vr - ei * vi;
+    ai = ai + er * vi + ei * vr;
+}
+
 // Epilogue shared by every family: y = alpha h + gamma z (+ sum_j g_j w_j),
 // store / accumulate, FP64 partial dots of (x, y), and the on-site field
 // gradient.  zv and av were loaded at the top of the element
@@ -265,7 +272,7 @@ __device__ __forceinline__ cplx<T> ld_row_nt(const cplx<T>* row, uint32_t boff) 
 template <typename T, typename VT>
 __device__ __forceinline__ void epilogue_ep(const KArgs<T, VT>& a, const unsigned ep, int64_t e, int64_t gidx,
                                             int glane, cplx<T> xc, cplx<T> zv, cplx<T> av, T hr, T hi, T alT, T gaT,
-                                            T er, T ei, T e0r, T e0i, int c, double& dxx, double& dxr, double& dxi,
+                                            T er, T ei, int c, double& dxx, double& dxr, double& dxi,
                                             double& dyy) {
     T yr = alT * hr, yi = alT * hi;
     yr += (gaT != T(0)) ? gaT * zv.re : T(0);
@@ -284,11 +291,12 @@ __device__ __forceinline__ void epilogue_ep(const KArgs<T, VT>& a, const unsigne
         }
     }
     if (ep & EP_STORE_Y) st_nt(a.y + e, yr, yi);
-    if (ep & EP_ACC_INIT) {
-        st_nt(a.acc_out + e, e0r * xc.re - e0i * xc.im + er * yr - ei * yi,
-              e0r * xc.im + e0i * xc.re + er * yi + ei * yr);
-    } else if (ep & EP_ACC_ADD) {
-        st_nt(a.acc_out + e, av.re + er * yr - ei * yi, av.im + er * yi + ei * yr);
+    if (ep & (EP_ACC_INIT | EP_ACC_ADD)) {
+        T ar = (ep & EP_ACC_ADD) ? av.re : T(0), ai = (ep & EP_ACC_ADD) ? av.im : T(0);
+        if (ep & EP_ACC_Z) add_term(ar, ai, T(a.etaz_re), T(a.etaz_im), zv.re, zv.im);
+        if (ep & EP_ACC_X) add_term(ar, ai, T(a.etax_re), T(a.etax_im), xc.re, xc.im);
+        add_term(ar, ai, er, ei, yr, yi);
+        st_nt(a.acc_out + e, ar, ai);
     }
     if (ep & (EP_DOTS | EP_MOMENTS)) {
         const double xr = double(xc.re), xi = double(xc.im);
@@ -310,9 +318,9 @@ __device__ __forceinline__ void epilogue_ep(const KArgs<T, VT>& a, const unsigne
 
 template <typename T, typename VT>
 __device__ __forceinline__ void epilogue(const KArgs<T, VT>& a, int64_t e, int64_t gidx, int glane, cplx<T> xc,
-                                         cplx<T> zv, cplx<T> av, T hr, T hi, T alT, T gaT, T er, T ei, T e0r,
-                                         T e0i, int c, double& dxx, double& dxr, double& dxi, double& dyy) {
-    epilogue_ep(a, a.ep, e, gidx, glane, xc, zv, av, hr, hi, alT, gaT, er, ei, e0r, e0i, c, dxx, dxr, dxi, dyy);
+                                         cplx<T> zv, cplx<T> av, T hr, T hi, T alT, T gaT, T er, T ei, int c,
+                                         double& dxx, double& dxr, double& dxi, double& dyy) {
+    epilogue_ep(a, a.ep, e, gidx, glane, xc, zv, av, hr, hi, alT, gaT, er, ei, c, dxx, dxr, dxi, dyy);
 }
 
 template <typename T>
@@ -416,7 +424,7 @@ __device__ __forceinline__ void sweep_block(const KArgs<T, VT>& a, int b_out, in
         ga = a.colp[3 * c + 2];
     }
     const T alT = T(al), beT = T(be), gaT = T(ga);
-    const T er = T(a.eta_re), ei = T(a.eta_im), e0r = T(a.eta0_re), e0i = T(a.eta0_im);
+    const T er = T(a.eta_re), ei = T(a.eta_im);
 
     // diagonal of the on-site block for this lane's row
     const int nt_onsite = (P::FAMILY != FAM_GENERIC) ? P::NT : a.n_terms;
@@ -544,8 +552,7 @@ __device__ __forceinline__ void sweep_block(const KArgs<T, VT>& a, int b_out, in
         }
         const int64_t site = (int64_t)row * a.Lx + x;
         const int64_t gidx = a.ggroup == nb ? site * NO + o : site;
-        epilogue(a, rb + xe, gidx, tid & (a.ggroup - 1), xc, zv, av, hr, hi, alT, gaT, er, ei, e0r, e0i, c, dxx, dxr,
-                 dxi, dyy);
+        epilogue(a, rb + xe, gidx, tid & (a.ggroup - 1), xc, zv, av, hr, hi, alT, gaT, er, ei, c, dxx, dxr, dxi, dyy);
     }
 
     if (a.ep & (EP_DOTS | EP_MOMENTS)) {
@@ -948,8 +955,14 @@ __device__ __forceinline__ void staged_epilogue(const KArgs<T, VT>& a, int64_t e
         yo[2 * q] = yr;
         yo[2 * q + 1] = yi;
         if constexpr ((EPM & EP_ACC_ADD) != 0u) {
-            ao[2 * q] = acc.v[q].re + er * yr - ei * yi;
-            ao[2 * q + 1] = acc.v[q].im + er * yi + ei * yr;
+            T ar = acc.v[q].re, ai = acc.v[q].im;
+            if constexpr ((EPM & EP_ACC_Z) != 0u)
+                add_term(ar, ai, T(a.etaz_re), T(a.etaz_im), z.v[q].re, z.v[q].im);
+            if constexpr ((EPM & EP_ACC_X) != 0u)
+                add_term(ar, ai, T(a.etax_re), T(a.etax_im), x.v[q].re, x.v[q].im);
+            add_term(ar, ai, er, ei, yr, yi);
+            ao[2 * q] = ar;
+            ao[2 * q + 1] = ai;
         }
         if constexpr ((EPM & (EP_DOTS | EP_MOMENTS)) != 0u) {
             const double xr = double(x.v[q].re), xi = double(x.v[q].im);
@@ -997,7 +1010,7 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
         ga = a.colp[3 * c + 2];
     }
     const T alT = T(al), beT = T(be), gaT = T(ga);
-    const T er = T(a.eta_re), ei = T(a.eta_im), e0r = T(a.eta0_re), e0i = T(a.eta0_im);
+    const T er = T(a.eta_re), ei = T(a.eta_im);
     const int nt_on = GEN ? a.n_terms : P::NT;   // index of the on-site block
     const T dgr = T(a.coef[(((size_t)nt_on * NO + o) * NO + o) * 2]);
     const T dgi = T(a.coef[(((size_t)nt_on * NO + o) * NO + o) * 2 + 1]);
@@ -1220,7 +1233,7 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
                         const int64_t st = rowi * a.Lx + (xe >> logsite);
                         const int64_t gidx = a.ggroup == a.nb ? st * NO + o : st;
                         epilogue_ep(a, ep, rb + xe, gidx, tid & (a.ggroup - 1), xs_[k].v[0], zv[k].v[0], av[k].v[0],
-                                    hv[k].v[0].re, hv[k].v[0].im, alT, gaT, er, ei, e0r, e0i, c, dxx[0], dxr[0],
+                                    hv[k].v[0].re, hv[k].v[0].im, alT, gaT, er, ei, c, dxx[0], dxr[0],
                                     dxi[0], dyy[0]);
                     } else {
                         staged_epilogue<EPM>(a, rb + (int64_t(xe) << S::LW), xs_[k], zv[k], av[k], hv[k], alT, gaT, er,
@@ -1384,8 +1397,10 @@ void make_kargs(const SweepParams& p, bool whole_part, KArgs<T, VT>& a) {
     a.gamma = p.gamma;
     a.eta_re = p.eta_re;
     a.eta_im = p.eta_im;
-    a.eta0_re = p.eta0_re;
-    a.eta0_im = p.eta0_im;
+    a.etax_re = p.etax_re;
+    a.etax_im = p.etax_im;
+    a.etaz_re = p.etaz_re;
+    a.etaz_im = p.etaz_im;
     a.ep = p.ep;
     {
         // a requested count below the default would need more partial-dot
@@ -1554,7 +1569,7 @@ hipError_t launch_staged(SweepParams& p, int num_cus, hipStream_t s) {
 // every other combination with the flags read at run time.
 template <class P, typename T, typename VT, int E>
 hipError_t launch_staged_ep(SweepParams& p, int nt, int num_cus, hipStream_t s) {
-    constexpr unsigned KPM = EP_STORE_Y | EP_MOMENTS, DOTS = EP_STORE_Y | EP_DOTS, SERIES = EP_STORE_Y | EP_ACC_ADD,
+    constexpr unsigned KPM = EP_STORE_Y | EP_MOMENTS, DOTS = EP_STORE_Y | EP_DOTS, SERIES = EP_SERIES,
                        PLAIN = EP_STORE_Y;
     if (p.colp == nullptr) {
         if constexpr (P::FAMILY != FAM_GENERIC) {
@@ -1634,7 +1649,8 @@ StagedTile staged_tile(const SweepParams& p) {
     const StagedTile t0{e0, p.st_nt == 512 ? 512 : kBlock};
     if (P::FAMILY == FAM_GENERIC || p.st_E > 0 || p.st_nt > 0 || env_e > 0 || p.colp != nullptr) return t0;
     const int64_t n = p.L[0] * p.L[1] * p.L[2] * P::NO * p.nb;
-    const bool series = p.ep == (EP_STORE_Y | EP_ACC_ADD), step = p.ep == (EP_STORE_Y | EP_DOTS) || p.ep == (EP_STORE_Y | EP_MOMENTS);
+    const bool series = p.ep == EP_SERIES;
+    const bool step = p.ep == (EP_STORE_Y | EP_DOTS) || p.ep == (EP_STORE_Y | EP_MOMENTS);
     if (n < (int64_t(1) << 22) || !(series || step || p.ep == EP_STORE_Y)) return t0;
     if (P::DIM == 2) return {2 * e0, 512};
     const bool c128 = sizeof(T) == 8, walks = n >= (int64_t(1) << 24) && p.L[2] >= 32;
