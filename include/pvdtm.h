@@ -676,7 +676,8 @@ pv_status pv_autotune(pv_lattice *lat, int dtype, int nb, const char *cache_path
  * kernel, elements per lane and lanes per workgroup of pv_tuning (other
  * fields are ignored: each instance walks whole columns of its lattice with
  * workgroups of its own).  Unset, a batch takes lattice 0's kernel and
- * elements per lane with 256-lane workgroups.  Setting or resetting (t ==
+ * elements per lane, where those are unset the library's choice for the
+ * batch as a whole, with 256-lane workgroups.  Setting or resetting (t ==
  * NULL) drops the captured graph.  512-lane workgroups need a compiled
  * stencil family or generated kernels (PV_ERR_UNSUPPORTED otherwise).  A
  * batch of generic-stencil lattices takes generated kernels (compiled

@@ -2502,40 +2502,67 @@ bool batch_codegen(const pv_batch* B) {
     return true;
 }
 
+// Elements per lane of a staged batch whose shape leaves them open: the longer
+// tile where every CU still gets six walks of it (built-in families; walks are
+// whole columns, so nothing else balances the launch).  us per step, short |
+// long: TI c64 nb 16 64^3 x 12 (3072 walks) 975 | 912, c128 nb 8 32^3 x 64
+// (4096) 670 | 633; c64 nb 4 96^3 x 4 (768) 321 | 377.
+int batch_elems(const pv_batch* B, int dtype, int nb) {
+    const int longer = dtype == PV_C128 ? 2 : 4;
+    if (B->family == pv::FAM_GENERIC) return 0;
+    int64_t walks = 0;
+    for (const pv_lattice* l : B->lats) {
+        const int64_t nxs = (l->L[0] * l->n_orb * nb + 256 * longer - 1) / (256 * longer);
+        const int64_t nm = l->dim == 3 ? (l->L[1] >= 8 ? (l->L[1] + 7) / 8 : l->L[1]) : 1;
+        walks += 8 * nm * nxs;
+    }
+    return walks >= 6 * 256 ? longer : 0;
+}
+
 // Launch description of instance i of a batch (every instance takes the
-// batch's shape).
-pv::SweepParams batch_params(const pv_batch* B, int i, int dtype, int nb) {
+// batch's shape; elems: what it leaves open).
+pv::SweepParams batch_params(const pv_batch* B, int i, int dtype, int nb, int elems) {
     pv::SweepParams p = base_params(B->lats[i], dtype, nb);
     if (!batch_codegen(B)) p.cg_src = nullptr;
     p.vtype = (dtype == PV_C128) ? 0 : B->lats[i]->vtype;
     const pv_tuning t = batch_shape(B, dtype, nb);
     p.kernel = t.kernel;
-    p.st_E = t.elems_per_lane;
+    p.st_E = t.elems_per_lane > 0 || t.workgroup_size > 0 ? t.elems_per_lane : elems;
     p.st_nt = t.workgroup_size;
     return p;
 }
 
-// The staged kernel serves a batch unless its shape asks for the direct one;
-// by default only batches of instances averaging at least 2^20 elements per
-// block (smaller ones are launch-latency bound).
+// The staged kernel serves a batch unless its shape asks for the direct one; by
+// default only batches of at least 72 * 1024 elements for each plane of the
+// longest walk: a walk takes about 1.3 us per plane however little runs beside
+// it, the direct kernel 18 (complex64) to 25 us per 2^20 elements.  us per step,
+// TI, direct | staged: c64 nb 4 24^3 x 3 (27 * 1024) 17.6 | 29.9, 24^3 x 8 (72 *
+// 1024) 41.5 | 34.6, nb 8 24^3 x 8 61.5 | 41.7, nb 1 32^3 x 64 234 | 146;
+// c128 nb 8 16^3 x 16 (128 * 1024) 52 | 33; nb 1, 20 to 56 cubed (42 * 1024) 75 | 79.
 bool batch_may_stage(const pv_batch* B, int dtype, int nb) {
     static const char* env = std::getenv("PV_SWEEP");
     if ((B->family == pv::FAM_GENERIC && !batch_codegen(B)) || (env && std::atoi(env) == 1)) return false;
     if (B->n_orb * nb > pv::STAGED_MAX_SITE) return false;
     const int kind = batch_shape(B, dtype, nb).kernel;
     if (kind != 0 || (env && std::atoi(env) == 2)) return kind != 1;
-    int64_t elems = 0;
-    for (const pv_lattice* l : B->lats) elems += l->n_rows * nb;
-    return elems / int64_t(B->lats.size()) >= (int64_t(1) << 20);
+    int64_t elems = 0, planes = 1;
+    for (const pv_lattice* l : B->lats) {
+        elems += l->n_rows * nb;
+        const bool parts = l->dim == 2 || l->L[1] < 8;   // the outer axis in eighths
+        const int64_t Lw = l->L[l->dim - 1];
+        planes = std::max(planes, parts ? (Lw + 7) / 8 : Lw);
+    }
+    return elems >= planes * 72 * 1024;
 }
 
 pv_status batch_counts(const pv_batch* B, int dtype, int nb, int staged, std::vector<int>& nblocks, int& total) {
     const int n = int(B->lats.size());
     nblocks.assign(n, 0);
     total = 0;
+    const int elems = batch_elems(B, dtype, nb);
     std::vector<char> rec(pv::batch_record_bytes());
     for (int i = 0; i < n; ++i) {
-        const pv::SweepParams p = batch_params(B, i, dtype, nb);
+        const pv::SweepParams p = batch_params(B, i, dtype, nb, elems);
         if (pv::batch_fill_record(p, staged, rec.data(), &nblocks[i]) != hipSuccess)
             return fail(PV_ERR_UNSUPPORTED, "instance %d: unsupported field / vector type combination", i);
         total += nblocks[i];
@@ -2552,8 +2579,13 @@ pv_status batch_layout(const pv_batch* B, int dtype, int nb, int M, int staged, 
     std::vector<int> nd, ns;
     int td = 0, ts = 0;
     if ((st = batch_counts(B, dtype, nb, 0, nd, td)) != PV_OK) return st;
-    const bool may = batch_may_stage(B, dtype, nb);
+    bool may = batch_may_stage(B, dtype, nb);
     if (may && (st = batch_counts(B, dtype, nb, 1, ns, ts)) != PV_OK) return st;
+    // chosen here, it needs no more partial dots than the direct kernel
+    if (may && ts > td && batch_shape(B, dtype, nb).kernel == 0) {
+        may = false;
+        ts = 0;
+    }
     L.staged = staged && may;
     L.nblocks = L.staged ? ns : nd;
     L.total_blocks = L.staged ? ts : td;
@@ -2683,6 +2715,7 @@ extern "C" pv_status pv_batch_kpm_moments(pv_batch* B, int dtype, int nb, int M,
     PV_HIP(hipStreamSynchronize(s));
 
     char* w = static_cast<char*>(work);
+    const int elems = batch_elems(B, dtype, nb);
     const size_t rb = pv::batch_record_bytes();
     std::vector<char> tables(4 * (size_t)n * rb);
     std::vector<int> block_inst(L.total_blocks), inst_block0(n + 1);
@@ -2697,7 +2730,7 @@ extern "C" pv_status pv_batch_kpm_moments(pv_batch* B, int dtype, int nb, int M,
         void* A = w + L.vec_off[i];
         void* Bv = w + L.vec_off[i] + vec_bytes(l, dtype, nb);
         for (int v = 0; v < 4; ++v) {
-            pv::SweepParams p = batch_params(B, i, dtype, nb);
+            pv::SweepParams p = batch_params(B, i, dtype, nb, elems);
             p.zero_row = l->d_zero;
             p.slab_rows = slab_rows(l, dtype, nb);
             // variants 0 and 2 run even steps, 1 and 3 odd ones; dots into the
@@ -2736,7 +2769,7 @@ extern "C" pv_status pv_batch_kpm_moments(pv_batch* B, int dtype, int nb, int M,
     for (int i = 1; i < n; ++i)
         if (dtype != PV_C128 && B->lats[i]->vtype != vtype && (B->lats[i]->V || B->lats[0]->V))
             return fail(PV_ERR_UNSUPPORTED, "all instances of a batch need the same field type");
-    pv::SweepParams p0 = batch_params(B, 0, dtype, nb);
+    pv::SweepParams p0 = batch_params(B, 0, dtype, nb, elems);
     p0.vtype = vtype;
     p0.ep = pv::EP_STORE_Y | pv::EP_MOMENTS;
     // a generated kernel is compiled and loaded before the capture
