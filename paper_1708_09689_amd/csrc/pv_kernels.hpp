@@ -50,6 +50,7 @@ enum : unsigned {
     EP_MOMENTS = 128u,   // per-block partial dots (xx, Re xy): what KPM moments take
     EP_GTERMS = 16u,     // y += sum_j gcoef[j][c] gw_j (adjoint source terms)
     EP_GRAD = 32u,       // grad += gx Re(conj(x) gw_1) + gy Re(conj(y) gw_0) per site/row
+    EP_ADJOINT = 1u | 16u | 32u,   // a step of the adjoint recurrence
     EP_NO_Z = 64u,       // launch-internal: gamma = 0, z is neither loaded nor staged
 };
 

@@ -722,6 +722,8 @@ struct StagedSide {
     static constexpr int SLEN = HALO ? S::RCH * NT * S::CE : S::TW;     // LDS elements per row
     u32x4 side[NTR > 0 ? NTR : 1][SCH];
     u32x4 acc[S::TCH];
+    u32x4 gw[3][S::TCH];   // adjoint steps: the three source vectors
+    double grad[S::EL];    // and the gradient entries
 };
 
 // Stencils whose rows differ along one axis at a time: the kernel can walk along
@@ -735,7 +737,7 @@ __host__ __device__ constexpr bool walks_either() {
 }
 
 // ZL: the step reads z (every epilogue but the plain sweep with gamma = 0)
-template <class P, typename T, typename VT, int E, bool ACC, int NT, int W, bool ZL = true>
+template <class P, typename T, typename VT, int E, bool ACC, int NT, int W, bool ZL = true, bool ADJ = false>
 struct StagedCtx {
     using S = Staged<T, E, NT, W>;
     using El = Elem<T, W>;
@@ -756,6 +758,7 @@ struct StagedCtx {
     uint32_t roff[S::RCH] = {};
     uint32_t soff[S::TCH] = {};
     uint32_t voff[EL] = {};
+    uint32_t goff[EL] = {};   // adjoint steps: gradient entries inside a row
     int vshift = 0;  // element -> field entry: log2 of elements per site or per orbital row
 
     __device__ __forceinline__ int64_t row_of(int mm, int ww) const {
@@ -806,6 +809,17 @@ struct StagedCtx {
             if (r >= vlen) r = vlen - 1;
             voff[k] = uint32_t(r);
         }
+        if constexpr (ADJ) {
+#pragma unroll
+            for (int k = 0; k < EL; ++k) {
+                int g = xe0 + tid + k * S::NTH;
+                if (g >= rowel) g = rowel - 1;
+                goff[k] = uint32_t(g) >> __builtin_ctz(a.ggroup);   // a power of two
+            }
+        }
+    }
+    __device__ __forceinline__ double* grad_row(int64_t row) const {
+        return a.grad + row * (a.rowel >> __builtin_ctz(a.ggroup));
     }
     // Issue the loads of ring row (m, w_ring) and of the per-step rows of
     // outer index w_row (clamped to the walk) into the set.  Every load is
@@ -837,6 +851,18 @@ struct StagedCtx {
             const cplx<T>* ar = a.asrc + row_of(m, wr) * a.rowel;
 #pragma unroll
             for (int k = 0; k < S::TCH; ++k) sd.acc[k] = ld_chunk_nt<T>(ar, soff[k]);
+        }
+        if constexpr (ADJ) {
+            const int64_t rw = row_of(m, w_row < wb ? w_row : wb - 1);
+#pragma unroll
+            for (int k = 0; k < S::TCH; ++k) {
+                sd.gw[0][k] = ld_chunk_nt<T>(a.gw0 + rw * a.rowel, soff[k]);
+                sd.gw[1][k] = ld_chunk_nt<T>(a.gw1 + rw * a.rowel, soff[k]);
+                sd.gw[2][k] = ld_chunk_nt<T>(a.gw2 + rw * a.rowel, soff[k]);
+            }
+            const double* gr = grad_row(rw);
+#pragma unroll
+            for (int k = 0; k < EL; ++k) sd.grad[k] = gr[goff[k]];
         }
         if constexpr (NTR > 0) {
             const int wr = w_row < wb ? w_row : wb - 1;
@@ -983,11 +1009,13 @@ template <class P, typename T, typename VT, int E, unsigned EPM, int NT, int W>
 __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, int part, int jb, int G) {
     using S = Staged<T, E, NT, W>;
     using El = Elem<T, W>;
-    static_assert(EPM != 0u || W == 1, "the run-time epilogue has elements of one column");
+    constexpr bool ADJ = EPM == EP_ADJOINT;
+    static_assert((EPM != 0u && !ADJ) || W == 1, "these epilogues have elements of one column");
     constexpr int EL = S::EL;
     constexpr bool ACC = EPM == 0u || (EPM & EP_ACC_ADD) != 0u;
     constexpr bool ZL = (EPM & EP_NO_Z) == 0u;
-    using Ctx = StagedCtx<P, T, VT, E, ACC, NT, W, ZL>;
+    using Ctx = StagedCtx<P, T, VT, E, ACC, NT, W, ZL, ADJ>;
+    static_assert(!ADJ || S::ZR, "adjoint steps take their vectors from registers");
     using Set = typename Ctx::Set;
     constexpr int NO = P::NO;
     constexpr int NTR = Ctx::NTR;
@@ -1020,6 +1048,14 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
     int dq[NS > 0 ? NS : 1];
     slot_coefficients<P, T, NS>(a.coef, o, nb, cre, cim, dq);
     double dxx[W] = {}, dxr[W] = {}, dxi[W] = {}, dyy[W] = {};
+    T gcr[3] = {}, gci[3] = {};   // coefficients of the adjoint source terms
+    if constexpr (ADJ) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            gcr[j] = T(a.gcoef[(j * a.nb + c) * 2]);
+            gci[j] = T(a.gcoef[(j * a.nb + c) * 2 + 1]);
+        }
+    }
 
     // generic stencils: offsets and the nonzero entries of every block row
     // (packed by the host after the offsets and the dense blocks) in LDS
@@ -1099,12 +1135,18 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
         cx.commit(A, 2);
         cx.commit_side(SD);
         El zc[EL], ac[EL];   // z and acc of the step at hand (ZR)
+        El gc[3][EL];        // and what an adjoint step reads
+        double gradc[EL];
         auto take = [&](const Set& st) {
             if constexpr (S::ZR) {
 #pragma unroll
                 for (int k = 0; k < EL; ++k) {
                     if constexpr (ZL) zc[k] = __builtin_bit_cast(El, st.z[k]);
                     if constexpr (ACC) ac[k] = __builtin_bit_cast(El, SD.acc[k]);
+                    if constexpr (ADJ) {
+                        for (int j = 0; j < 3; ++j) gc[j][k] = __builtin_bit_cast(El, SD.gw[j][k]);
+                        gradc[k] = SD.grad[k];
+                    }
                 }
             }
         };
@@ -1131,7 +1173,8 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
             const El* zhi = a.st_ywalk ? cx.tra + Ctx::Side::SLEN : rp;
             const int64_t rowi = cx.row_of(cx.m, w);
             const int64_t rb = rowi * a.rowel;
-            El hv[EL], xs_[EL], zv[EL], av[EL];
+            El hv[EL], xs_[EL], zv[EL], av[EL], gv[3][EL];
+            double gradv[EL];
 #pragma unroll
             for (int k = 0; k < EL; ++k) {
                 const int l = tid + k * NT;
@@ -1220,6 +1263,10 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
                 else zv[k] = El{};
                 if constexpr (ACC) av[k] = S::ZR ? ac[k] : cx.al[l];
                 else av[k] = El{};
+                if constexpr (ADJ) {
+                    for (int j = 0; j < 3; ++j) gv[j][k] = gc[j][k];
+                    gradv[k] = gradc[k];
+                }
             }
             lds_barrier();
             cx.commit(cur, (s + 3) % 3);
@@ -1235,6 +1282,25 @@ __device__ __forceinline__ void staged_block(const KArgs<T, VT>& a, int b_out, i
                         epilogue_ep(a, ep, rb + xe, gidx, tid & (a.ggroup - 1), xs_[k].v[0], zv[k].v[0], av[k].v[0],
                                     hv[k].v[0].re, hv[k].v[0].im, alT, gaT, er, ei, c, dxx[0], dxr[0],
                                     dxi[0], dyy[0]);
+                    } else if constexpr (ADJ) {
+                        // the operations of epilogue_ep
+                        const cplx<T> xc = xs_[k].v[0], zc1 = zv[k].v[0];
+                        T yr = alT * hv[k].v[0].re, yi = alT * hv[k].v[0].im;
+                        yr += (gaT != T(0)) ? gaT * zc1.re : T(0);
+                        yi += (gaT != T(0)) ? gaT * zc1.im : T(0);
+#pragma unroll
+                        for (int j = 0; j < 3; ++j) {
+                            const cplx<T> g = gv[j][k].v[0];
+                            yr += gcr[j] * g.re - gci[j] * g.im;
+                            yi += gcr[j] * g.im + gci[j] * g.re;
+                        }
+                        st_nt(a.y + rb + xe, yr, yi);
+                        const cplx<T> g0 = gv[0][k].v[0], g1 = gv[1][k].v[0];
+                        double g = a.gx * (double(xc.re) * double(g1.re) + double(xc.im) * double(g1.im)) +
+                                   a.gy * (double(yr) * double(g0.re) + double(yi) * double(g0.im));
+                        for (int mm = 1; mm < a.ggroup; mm <<= 1) g += __shfl_xor(g, mm);
+                        if ((tid & (a.ggroup - 1)) == 0)
+                            cx.grad_row(rowi)[cx.goff[k]] = gradv[k] + g;
                     } else {
                         staged_epilogue<EPM>(a, rb + (int64_t(xe) << S::LW), xs_[k], zv[k], av[k], hv[k], alT, gaT, er,
                                              ei, dxx, dxr, dxi, dyy);
@@ -1567,6 +1633,18 @@ hipError_t launch_staged(SweepParams& p, int num_cus, hipStream_t s) {
 // fused dots (KPM), the series step (propagation, filters), the plain sweep
 // or Chebyshev step without dots (with gamma = 0: no z stream at all), and
 // every other combination with the flags read at run time.
+// Whether a launch is the adjoint step of a gradient with everything that the
+// staged kernel reads a step ahead: all three sources, in 16-byte elements.
+// Bound by its 7 vector streams; the direct kernel also re-reads its neighbours
+// through the caches: TI 64^3 nb 8 182 us per step, staged 136 (6.0 TB/s).
+template <class P, typename T>
+bool staged_adjoint(const SweepParams& p) {
+    if (sizeof(T) != 8 || P::FAMILY == FAM_GENERIC || p.ep != EP_ADJOINT || p.colp != nullptr || !p.z) return false;
+    const uintptr_t all = reinterpret_cast<uintptr_t>(p.gw[0]) | reinterpret_cast<uintptr_t>(p.gw[1]) |
+                          reinterpret_cast<uintptr_t>(p.gw[2]) | reinterpret_cast<uintptr_t>(p.z);
+    return p.gw[0] && p.gw[1] && p.gw[2] && (all & 15) == 0;
+}
+
 template <class P, typename T, typename VT, int E>
 hipError_t launch_staged_ep(SweepParams& p, int nt, int num_cus, hipStream_t s) {
     constexpr unsigned KPM = EP_STORE_Y | EP_MOMENTS, DOTS = EP_STORE_Y | EP_DOTS, SERIES = EP_SERIES,
@@ -1589,6 +1667,9 @@ hipError_t launch_staged_ep(SweepParams& p, int nt, int num_cus, hipStream_t s) 
             return p.gamma == 0.0 ? launch_staged<P, T, VT, E, PLAIN | EP_NO_Z>(p, num_cus, s)
                                   : launch_staged<P, T, VT, E, PLAIN>(p, num_cus, s);
     }
+    if constexpr (sizeof(T) == 8 && E == 1 && P::FAMILY != FAM_GENERIC) {
+        if (staged_adjoint<P, T>(p)) return launch_staged<P, T, VT, 1, EP_ADJOINT>(p, num_cus, s);
+    }
     if constexpr (sizeof(T) == 8 && E == 2) {
         // the run-time epilogue at two complex128 elements per lane needs more
         // than 256 VGPRs: one element per lane, default walk and workgroups
@@ -1603,15 +1684,15 @@ hipError_t launch_staged_ep(SweepParams& p, int nt, int num_cus, hipStream_t s) 
 }
 
 // Epilogues the staged kernel takes by default: plain sweeps, the Chebyshev
-// step with dots and the series steps.  The adjoint epilogues (extra vector
-// terms and the field gradient) default to the direct kernel, which issues
-// their loads together with the neighbour loads.
+// step with dots and the series steps; adjoint steps with all three sources
+// where launch_typed says so, other adjoint epilogues take the direct kernel,
+// which issues their loads together with the neighbour loads.
 // Small blocks (below 2^20 elements, cache resident) are launch-latency
 // bound, where the direct kernel's single pass beats the staged walks.
-bool staged_default(const SweepParams& p) {
-    const int64_t elems = p.L[0] * p.L[1] * p.L[2] * p.n_orb * p.nb;
-    return (p.ep & (EP_GTERMS | EP_GRAD)) == 0 && elems >= (int64_t(1) << 20);
+bool large_block(const SweepParams& p) {
+    return p.L[0] * p.L[1] * p.L[2] * p.n_orb * p.nb >= (int64_t(1) << 20);
 }
+bool staged_default(const SweepParams& p) { return (p.ep & (EP_GTERMS | EP_GRAD)) == 0 && large_block(p); }
 
 // Elements per lane of a staged launch that asks for none: one for complex128,
 // two for complex64 (one 16-byte chunk per lane and row either way).
@@ -1681,7 +1762,12 @@ hipError_t launch_typed(SweepParams& p, int num_cus, hipStream_t s) {
         const bool aligned = ((reinterpret_cast<uintptr_t>(p.x) | reinterpret_cast<uintptr_t>(p.zero_row)) & 15) == 0;
         // generic stencils default to staged only on 3D lattices (walks along z)
         const bool can = P::FAMILY != FAM_GENERIC || p.generic_stageable;
-        const bool dflt = staged_default(p) && (P::FAMILY != FAM_GENERIC || p.L[2] > 1);
+        // Weyl adjoint steps stay direct unless asked for: their few neighbours
+        // cost little there, and ragged rows more here (gradient at 64^3 nb 16
+        // 4.66 ms direct, 4.24 staged; 100x90x40 nb 8 4.65 and 4.88)
+        const bool adj = P::FAMILY != FAM_WEYL && staged_adjoint<P, T>(p) && large_block(p);
+        const bool dflt = (staged_default(p) || adj) &&
+                          (P::FAMILY != FAM_GENERIC || p.L[2] > 1);
         // a site must be whole 16-byte chunks: ring rows start one site
         // before the tile and wrap by whole chunks (complex64 with
         // n_orb * nb = 1 is half a chunk per site: direct kernel)
