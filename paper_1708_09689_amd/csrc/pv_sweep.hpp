@@ -1635,8 +1635,8 @@ hipError_t launch_staged(SweepParams& p, int num_cus, hipStream_t s) {
 // every other combination with the flags read at run time.
 // Whether a launch is the adjoint step of a gradient with everything that the
 // staged kernel reads a step ahead: all three sources, in 16-byte elements.
-// Bound by its 7 vector streams; the direct kernel also re-reads its neighbours
-// through the caches: TI 64^3 nb 8 182 us per step, staged 136 (6.0 TB/s).
+// Bound by its 6 vector streams; the direct kernel also re-reads its neighbours
+// through the caches: TI 64^3 nb 8 182 us per step, staged 136 (5.9 TB/s).
 template <class P, typename T>
 bool staged_adjoint(const SweepParams& p) {
     if (sizeof(T) != 8 || P::FAMILY == FAM_GENERIC || p.ep != EP_ADJOINT || p.colp != nullptr || !p.z) return false;
