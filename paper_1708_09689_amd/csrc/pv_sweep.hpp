@@ -1636,7 +1636,7 @@ hipError_t launch_staged(SweepParams& p, int num_cus, hipStream_t s) {
 // Whether a launch is the adjoint step of a gradient with everything that the
 // staged kernel reads a step ahead: all three sources, in 16-byte elements.
 // Bound by its 6 vector streams; the direct kernel also re-reads its neighbours
-// through the caches: TI 64^3 nb 8 182 us per step, staged 136 (5.9 TB/s).
+// through the caches: TI 64^3 nb 8 182 us per step, staged 140 (5.7 TB/s).
 template <class P, typename T>
 bool staged_adjoint(const SweepParams& p) {
     if (sizeof(T) != 8 || P::FAMILY == FAM_GENERIC || p.ep != EP_ADJOINT || p.colp != nullptr || !p.z) return false;
