@@ -1502,20 +1502,24 @@ size_t staged_lds_bytes() {
 // workgroups idle costs about three tenths of what it would if they did not
 // leave their bandwidth to the others.
 struct StagedWalk {
-    int nm = 0, nW = 0, C = 1, items = 1;
+    int nm = 0, nW = 0, C = 1, items = 1, along_y = 0;
     double cost = 0.0;
-    StagedWalk(int Lm, int Lw, int nxs) {
+    StagedWalk(int Lm, int Lw, int nxs, int y) : along_y(y) {
         const bool split_m = Lm >= 8;
         nm = split_m ? (Lm + 7) / 8 : Lm;
         nW = split_m ? Lw : (Lw + 7) / 8;
         chunk(nW, nxs, 1);
     }
-    void chunk(int planes, int nxs, int G8) {
-        C = planes < nW ? planes : nW;
+    // last: what the last round costs of a whole one
+    double planes(int G8, double last) const {
+        const int rounds = (items + G8 - 1) / G8;
+        return ((1.0 - last) * std::max(1.0, double(items) / G8) + last * rounds) * (C + 2);
+    }
+    void chunk(int c, int nxs, int G8) {
+        C = c < nW ? c : nW;
         if (C < 1) C = 1;
         items = nW < 1 ? 1 : ((nW + C - 1) / C) * nm * nxs;
-        const int rounds = (items + G8 - 1) / G8;
-        cost = (0.7 * std::max(1.0, double(items) / G8) + 0.3 * rounds) * (C + 2);
+        cost = planes(G8, 0.3);
     }
 };
 
@@ -1528,35 +1532,41 @@ struct StagedWalk {
 //   TI c64 57x83x46 nb 8      step 56.8 | 43.0   plain 45.3 | 33.3   series 66.3 | 62.1   (5, 5, 2 chunks)
 // Along y with 8 planes or more the parts are single rows m, whose side rows
 // other XCDs load: 96x96x8 nb 16 step 54.0 | 58.0 at best.
+// nxs: column tiles per row.
+template <class P>
+StagedWalk staged_walk(const SweepParams& p, int nxs, int G8, bool full_walk) {
+    const int Ly = int(p.L[1]), Lz = int(p.L[2]);
+    StagedWalk k(P::DIM == 3 ? Ly : 1, P::DIM == 3 ? Lz : Ly, nxs, 0);
+    if (p.st_C > 0 || full_walk) {
+        k.chunk(full_walk && p.st_C <= 0 ? k.nW : p.st_C, nxs, 1);
+        return k;
+    }
+    auto fill = [&](const StagedWalk& from, StagedWalk& best) {
+        for (int nwc = 1; nwc <= 8; ++nwc) {
+            StagedWalk t = from;
+            t.chunk((t.nW + nwc - 1) / nwc, nxs, G8);
+            if (t.cost < best.cost) best = t;
+        }
+    };
+    const int cols = k.nm * nxs, n0 = std::max(1, std::min((G8 + cols - 1) / cols, k.nW));
+    k.chunk((k.nW + n0 - 1) / n0, nxs, G8);
+    if (p.st_Bm <= 0 && p.st_G8 <= 0) {
+        const StagedWalk k0 = k;
+        k.cost *= 0.92;
+        fill(k0, k);
+        if (walks_either<P>() && Lz < 8) fill(StagedWalk(Lz, Ly, nxs, 1), k);
+    }
+    return k;
+}
+
 template <class P, typename T, typename VT, int E, int NT, int W>
 int staged_setup(const SweepParams& p, int G8, bool full_walk, KArgs<T, VT>& a) {
     constexpr int TW = NT * E;   // complex numbers of a column tile
     a.st_site = P::NO * p.nb;
     a.st_seg = staged_seg<T, E, NT, W>();   // ring slot; its first elements hold the tile and two sites
     a.st_nxs = (a.rowel + TW - 1) / TW;
-    a.st_ywalk = 0;
-    StagedWalk k(P::DIM == 3 ? a.Ly : 1, P::DIM == 3 ? a.Lz : a.Ly, a.st_nxs);
-    if (p.st_C > 0 || full_walk) {
-        k.chunk(full_walk && p.st_C <= 0 ? k.nW : p.st_C, a.st_nxs, 1);
-    } else {
-        auto fill = [&](const StagedWalk& from, StagedWalk& best, int ywalk) {
-            for (int nwc = 1; nwc <= 8; ++nwc) {
-                StagedWalk t = from;
-                t.chunk((t.nW + nwc - 1) / nwc, a.st_nxs, G8);
-                if (t.cost >= best.cost) continue;
-                best = t;
-                a.st_ywalk = ywalk;
-            }
-        };
-        const int cols = k.nm * a.st_nxs, n0 = std::max(1, std::min((G8 + cols - 1) / cols, k.nW));
-        k.chunk((k.nW + n0 - 1) / n0, a.st_nxs, G8);
-        if (p.st_Bm <= 0 && p.st_G8 <= 0) {
-            const StagedWalk k0 = k;
-            k.cost *= 0.92;
-            fill(k0, k, 0);
-            if (walks_either<P>() && a.Lz < 8) fill(StagedWalk(a.Lz, a.Ly, a.st_nxs), k, 1);
-        }
-    }
+    const StagedWalk k = staged_walk<P>(p, a.st_nxs, G8, full_walk);
+    a.st_ywalk = k.along_y;
     a.st_C = k.C;
     if (P::DIM != 3) {
         a.st_Lm = 1; a.st_Lw = a.Ly; a.st_pm = 0; a.st_pw = a.py;
@@ -1706,25 +1716,32 @@ int staged_elems(const SweepParams& p) {
 
 // Tile of a staged launch of a built-in family that asks for no elements per
 // lane and no workgroup size.  Longer tiles re-read less x halo (two sites per
-// tile) and have more loads in flight, and pay once there are walks enough
-// for every CU: from 2^22 elements, and at 512 lanes (one workgroup per CU)
-// from 2^24 on walks of 32 planes.  us per sweep, short tile | long tile:
-//   TI c128 64^3 nb 8 (2^23)         step 88.5 | 77.2   plain 60.6 | 55.1
-//   TI c128 240x240x6 nb 32          step 548  | 533    plain 465  | 408  (512 lanes: 432)
-//   TI c128 256x256x64 nb 4          step 652  | 605    plain 514  | 446  (256 lanes: 473)
-//   TI c128 96x96x6 nb 8 (2^20.8)    step 30.0 | 32.4   plain 20.5 | 22.1: short
-//   TI c64 256x256x64 nb 4           step 352  | 293    plain 267  | 232
-//   TI c64 96x96x6 nb 32             step 49.9 | 47.8   plain 32.8 | 34.0: short walks
-//   Weyl c128 128x100x50 nb 8        step 125  | 106    plain 85.8 | 77.8
-//   graphene 512x512 c128 nb 32      step 330  | 276    plain 222  | 186   series 482 | 474
-// Series steps carry two more streams: at twice the registers per lane they
-// lose (TI c128 64^3 nb 8 113 | 129); with 512 lanes complex64 gains on long
-// walks (256x256x64 nb 4: 563 | 518) and complex128 does not (nb 8: 2122 | 2163).
+// tile) and have more loads in flight, but fill ragged rows worse and make
+// fewer walks, so each candidate's time is estimated as its walks' planes
+// (StagedWalk) times the numbers of its tiles, padding included, times a weight:
+// the ratio of times at equal work, with the share of a full round that the
+// last one costs (512 lanes leave one workgroup per CU, which nothing
+// balances).  Fitted to 454 launches on random and listed lattices of 2^22 to
+// 2^27 numbers, each with all three tiles: the chosen one is 0.6% from the best
+// on average, and more than 5% slower than the short one in 5 (at most 7%).
+// us per sweep: short | 2x | 2x with 512 lanes, * the choice:
+//   TI c128 256x256x64 nb 4      step 619 | 611 | 584*    plain 503 | 472 | 444*
+//   TI c128 264x256x64 nb 4      step 662 | 663* | 699    plain 522 | 502* | 543
+//   TI c128 64^3 nb 32           step 326 | 304 | 292*    plain 267 | 241 | 224*
+//   TI c128 72x64x64 nb 32       step 379 | 376* | 413    plain 309 | 299* | 324
+//   TI c128 64^3 nb 8            step 83 | 71* | 73       plain 62 | 54* | 58
+//   TI c128 17x300x60 nb 16      step 210* | 235 | 342    plain 184* | 194 | 296
+//   TI c64 256x256x64 nb 4       step 320 | 275* | 288    plain 267 | 226* | 234
+//   TI c64 65^3 nb 8             step 61* | 73 | 91       plain 50* | 61 | 79
+//   Weyl c128 130x130x60 nb 4    step 96* | 102 | 136     plain 72* | 87 | 122
+//   graphene 512x512 c128 nb 32  step 276 at 512 lanes, 330 short
+// The accumulating series step carries two more streams and keeps the short tile
+// in 3D: at twice the registers per lane it loses (TI c128 64^3 nb 8 113 | 129).
 struct StagedTile {
     int e, nt;
 };
 template <class P, typename T>
-StagedTile staged_tile(const SweepParams& p) {
+StagedTile staged_tile(const SweepParams& p, int num_cus) {
     static const int env_e = env_int("PV_STAGED_E", 0);
     const int e0 = staged_elems(p);
     const StagedTile t0{e0, p.st_nt == 512 ? 512 : kBlock};
@@ -1732,16 +1749,36 @@ StagedTile staged_tile(const SweepParams& p) {
     const int64_t n = p.L[0] * p.L[1] * p.L[2] * P::NO * p.nb;
     const bool series = p.ep == EP_SERIES;
     const bool step = p.ep == (EP_STORE_Y | EP_DOTS) || p.ep == (EP_STORE_Y | EP_MOMENTS);
-    if (n < (int64_t(1) << 22) || !(series || step || p.ep == EP_STORE_Y)) return t0;
-    if (P::DIM == 2) return {2 * e0, 512};
-    const bool c128 = sizeof(T) == 8, walks = n >= (int64_t(1) << 24) && p.L[2] >= 32;
-    if (P::FAMILY == FAM_TI) {
-        if (series) return {e0, walks && !c128 ? 512 : kBlock};
-        if (c128) return {2 * e0, walks ? 512 : kBlock};
-        return step || p.L[2] >= 32 || n >= (int64_t(1) << 25) ? StagedTile{2 * e0, kBlock} : t0;
+    if (n < (int64_t(1) << 22) || !(series || step || p.ep == EP_STORE_Y) || (series && P::DIM == 3)) return t0;
+    const int rowel = int(p.L[0]) * P::NO * p.nb;
+    auto time = [&](StagedTile t, double weight, double last) {
+        const int TW = t.nt * t.e, nxs = (rowel + TW - 1) / TW;
+        int G8 = p.st_G8 > 0 ? p.st_G8 : (num_cus >= 8 ? num_cus / 8 : 1) * (t.nt == kBlock ? 2 : 1);
+        if (G8 > 256) G8 = 256;
+        return weight * staged_walk<P>(p, nxs, G8, false).planes(G8, last) * G8 * TW;
+    };
+    StagedTile best = t0;
+    double t_best = time(t0, 1.0, 0.2);
+    auto consider = [&](int nt, double weight, double last) {
+        const StagedTile t{2 * e0, nt};
+        const double tt = time(t, weight, last);
+        if (tt < t_best) {
+            t_best = tt;
+            best = t;
+        }
+    };
+    const bool c128 = sizeof(T) == 8;
+    if (P::DIM == 2) {
+        consider(512, c128 ? 0.80 : 0.88, 0.9);
+    } else if (!c128) {
+        consider(kBlock, 0.82, 0.9);
+    } else if (n >= (int64_t(1) << 24)) {   // vectors of 256 MiB: halo re-reads miss the last-level cache
+        consider(kBlock, 0.92, 0.3);
+        consider(512, 0.90, 0.9);
+    } else {
+        consider(kBlock, 0.80, 0.5);
     }
-    if (series) return t0;
-    return c128 || (step && n >= (int64_t(1) << 23)) ? StagedTile{2 * e0, kBlock} : t0;
+    return best;
 }
 
 template <class X>
@@ -1773,7 +1810,7 @@ hipError_t launch_typed(SweepParams& p, int num_cus, hipStream_t s) {
         // n_orb * nb = 1 is half a chunk per site: direct kernel)
         const bool whole = (P::NO * p.nb * int(sizeof(cplx<T>))) % 16 == 0;
         if (can && aligned && whole && P::NO * p.nb <= STAGED_MAX_SITE && (kind == 2 || (kind == 0 && dflt))) {
-            const auto [e, nt] = staged_tile<P, T>(p);
+            const auto [e, nt] = staged_tile<P, T>(p, num_cus);
             auto staged = [&, e = e, nt = nt](auto pt) -> hipError_t {
                 using Q = typename decltype(pt)::type;
                 if constexpr (sizeof(T) == 8)

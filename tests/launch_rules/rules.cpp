@@ -1,0 +1,40 @@
+// Prints the launch rules' choices for the launches on stdin (built for the
+// host alone by tests/test_launch_rules.py; no kernel is instantiated).
+//   tile FAMILY DTYPE Lx Ly Lz NB EPILOGUE   ->   elements per lane, lanes
+#include <cstdio>
+#include <cstring>
+#include <string>
+
+#include "pv_sweep.hpp"
+
+namespace {
+
+template <class P>
+pv::StagedTile tile(const pv::SweepParams& p) {
+    return p.dtype == 0 ? pv::staged_tile<P, double>(p, 256) : pv::staged_tile<P, float>(p, 256);
+}
+
+}  // namespace
+
+int main() {
+    char what[16], name[32], ep[16];
+    while (std::scanf("%15s %31s", what, name) == 2) {
+        if (std::strcmp(what, "tile") == 0) {
+            pv::SweepParams p{};
+            long L[3];
+            if (std::scanf("%d %ld %ld %ld %d %15s", &p.dtype, &L[0], &L[1], &L[2], &p.nb, ep) != 6) return 1;
+            for (int k = 0; k < 3; ++k) p.L[k] = L[k];
+            const std::string e = ep, n = name;
+            p.ep = e == "step" ? pv::EP_STORE_Y | pv::EP_MOMENTS : (e == "plain" ? unsigned(pv::EP_STORE_Y) : unsigned(pv::EP_SERIES));
+            pv::StagedTile t{};
+            if (n == "ti") t = tile<pv::PatTI>(p);
+            else if (n == "weyl") t = tile<pv::PatWeyl>(p);
+            else if (n == "graphene4") t = tile<pv::PatGraphene4>(p);
+            else return 1;
+            std::printf("%d %d\n", t.e, t.nt);
+        } else {
+            return 1;
+        }
+    }
+    return 0;
+}

@@ -1,0 +1,61 @@
+"""The launch rules' choices (host code only; no GPU).
+
+A rule picks a kernel or a tile from the sizes of a launch.  The lattices here
+were timed with every choice (in the comments, microseconds on an MI355X); the
+rule takes the fastest, or one within the 5% that separates a choice from
+noise.  tests/launch_rules/rules.cpp prints the choices; it is compiled for
+the host from the sources of the library."""
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1708_09689_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    cxx = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(cxx):
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path_factory.mktemp("rules") / "rules")
+    cmd = [cxx, "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-I", CSRC, "-I", os.path.join(ROOT, "include"),
+           os.path.join(ROOT, "tests", "launch_rules", "rules.cpp"), "-o", exe]
+    done = subprocess.run(cmd, capture_output=True, text=True)
+    assert done.returncode == 0, done.stderr
+
+    def ask(line):
+        out = subprocess.run([exe], input=line + "\n", capture_output=True, text=True)
+        assert out.returncode == 0, line
+        return tuple(int(v) for v in out.stdout.split())
+
+    return ask
+
+
+# staged tile of a launch without a shape of its own: (elements per lane, lanes)
+TILES = [
+    # rows that fill long tiles, walks enough for 512-lane workgroups
+    ("ti 0 256 256 64 4 plain", (2, 512)),     # 503 short, 472 long, 444 long with 512 lanes
+    ("ti 0 64 64 64 32 step", (2, 512)),       # 326, 304, 292
+    ("ti 1 256 256 64 4 step", (4, 256)),      # 320, 275, 288
+    ("ti 0 64 64 64 8 step", (2, 256)),        # 83, 71, 73
+    # a last round of 512-lane workgroups that is mostly idle
+    ("ti 0 72 64 64 32 step", (2, 256)),       # 379, 376, 413
+    ("ti 0 264 256 64 4 plain", (2, 256)),     # 522, 502, 543
+    # rows that leave long tiles half empty
+    ("ti 0 17 300 60 16 step", (1, 256)),      # 210, 235, 342
+    ("ti 0 33 200 50 8 plain", (1, 256)),      # 93, 118, 153
+    ("ti 1 65 65 65 8 step", (2, 256)),        # 61, 73, 91
+    ("weyl 0 130 130 60 4 plain", (1, 256)),   # 72, 87, 122
+    # rows much shorter than any tile: a long one is empty lanes only
+    ("graphene4 0 8 200000 1 1 step", (1, 256)),
+    ("graphene4 0 512 512 1 32 step", (2, 512)),   # 330, -, 276
+]
+
+
+@pytest.mark.parametrize("launch,choice", TILES)
+def test_tile_of_a_staged_launch(rules, launch, choice):
+    assert rules("tile " + launch) == choice
