@@ -1500,7 +1500,8 @@ size_t staged_lds_bytes() {
 // planes it is `items` walks over G8 workgroups.  A walk costs its planes and
 // about two more to fill the ring, and a last round of walks that leaves
 // workgroups idle costs about three tenths of what it would if they did not
-// leave their bandwidth to the others.
+// leave their bandwidth to the others (one tenth with four workgroups on each
+// of an XCD's 32 CUs).
 struct StagedWalk {
     int nm = 0, nW = 0, C = 1, items = 1, along_y = 0;
     double cost = 0.0;
@@ -1519,7 +1520,7 @@ struct StagedWalk {
         C = c < nW ? c : nW;
         if (C < 1) C = 1;
         items = nW < 1 ? 1 : ((nW + C - 1) / C) * nm * nxs;
-        cost = planes(G8, 0.3);
+        cost = planes(G8, G8 > 96 ? 0.1 : 0.3);
     }
 };
 
@@ -1531,7 +1532,9 @@ struct StagedWalk {
 //   TI c128 240x240x6 nb 2    step 37.6 | 33.6   plain 30.1 | 27.4   series 50.2 | 45.6   (along y)
 //   TI c64 57x83x46 nb 8      step 56.8 | 43.0   plain 45.3 | 33.3   series 66.3 | 62.1   (5, 5, 2 chunks)
 // Along y with 8 planes or more the parts are single rows m, whose side rows
-// other XCDs load: 96x96x8 nb 16 step 54.0 | 58.0 at best.
+// other XCDs load: 96x96x8 nb 16 step 54.0 | 58.0 at best.  Below 2^21 numbers
+// the fewest chunks along w stay: TI c128 36x166x43 nb 2 plain 31.7 in three,
+// 37.6 in the four that would fill the round; 83x19x25 nb 8 20.6 and 22.8.
 // nxs: column tiles per row.
 template <class P>
 StagedWalk staged_walk(const SweepParams& p, int nxs, int G8, bool full_walk) {
@@ -1553,7 +1556,7 @@ StagedWalk staged_walk(const SweepParams& p, int nxs, int G8, bool full_walk) {
     if (p.st_Bm <= 0 && p.st_G8 <= 0) {
         const StagedWalk k0 = k;
         k.cost *= 0.92;
-        fill(k0, k);
+        if (p.L[0] * Ly * Lz * P::NO * p.nb >= (int64_t(1) << 21)) fill(k0, k);
         if (walks_either<P>() && Lz < 8) fill(StagedWalk(Lz, Ly, nxs, 1), k);
     }
     return k;

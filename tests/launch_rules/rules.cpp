@@ -1,6 +1,8 @@
 // Prints the launch rules' choices for the launches on stdin (built for the
 // host alone by tests/test_launch_rules.py; no kernel is instantiated).
 //   tile FAMILY DTYPE Lx Ly Lz NB EPILOGUE   ->   elements per lane, lanes
+//   walk FAMILY DTYPE Lx Ly Lz NB GROUPS     ->   planes per walk, 1 along y
+//                                                 (short tile, workgroups per XCD)
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -12,6 +14,12 @@ namespace {
 template <class P>
 pv::StagedTile tile(const pv::SweepParams& p) {
     return p.dtype == 0 ? pv::staged_tile<P, double>(p, 256) : pv::staged_tile<P, float>(p, 256);
+}
+
+template <class P>
+pv::StagedWalk walk(const pv::SweepParams& p, int G8) {
+    const int TW = p.dtype == 0 ? 256 : 512, rowel = int(p.L[0]) * P::NO * p.nb;
+    return pv::staged_walk<P>(p, (rowel + TW - 1) / TW, G8, false);
 }
 
 }  // namespace
@@ -32,6 +40,15 @@ int main() {
             else if (n == "graphene4") t = tile<pv::PatGraphene4>(p);
             else return 1;
             std::printf("%d %d\n", t.e, t.nt);
+        } else if (std::strcmp(what, "walk") == 0) {
+            pv::SweepParams p{};
+            long L[3];
+            int G8;
+            if (std::scanf("%d %ld %ld %ld %d %d", &p.dtype, &L[0], &L[1], &L[2], &p.nb, &G8) != 6) return 1;
+            for (int k = 0; k < 3; ++k) p.L[k] = L[k];
+            const std::string n = name;
+            const pv::StagedWalk w = n == "ti" ? walk<pv::PatTI>(p, G8) : walk<pv::PatWeyl>(p, G8);
+            std::printf("%d %d\n", w.C, w.along_y);
         } else {
             return 1;
         }

@@ -59,3 +59,20 @@ TILES = [
 @pytest.mark.parametrize("launch,choice", TILES)
 def test_tile_of_a_staged_launch(rules, launch, choice):
     assert rules("tile " + launch) == choice
+
+
+# walks of a staged launch on the short tile: (planes per walk, 1 along y).
+# 96 and 128 workgroups per XCD: three and four per CU.
+WALKS = [
+    ("weyl 1 65 65 65 16 128", (22, 0)),      # 22 planes 45.0, 13 planes 49.9
+    ("weyl 1 130 130 60 4 128", (20, 0)),     # 20 planes 42.8, 12 planes 47.2
+    ("weyl 1 100 90 40 8 128", (14, 0)),      # 14 planes 30.4, 8 planes 35.5
+    ("ti 0 36 166 43 2 96", (15, 0)),         # 15 planes 31.7, 11 planes 37.6
+    ("ti 1 57 83 46 8 96", (23, 0)),          # series steps: 23 planes 62.1, 46 planes 66.3
+    ("ti 0 240 240 6 32 64", (30, 1)),        # along y 346, along z 402
+]
+
+
+@pytest.mark.parametrize("launch,choice", WALKS)
+def test_walks_of_a_staged_launch(rules, launch, choice):
+    assert rules("walk " + launch) == choice
