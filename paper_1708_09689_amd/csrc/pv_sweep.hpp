@@ -1533,8 +1533,9 @@ struct StagedWalk {
 //   TI c64 57x83x46 nb 8      step 56.8 | 43.0   plain 45.3 | 33.3   series 66.3 | 62.1   (5, 5, 2 chunks)
 // Along y with 8 planes or more the parts are single rows m, whose side rows
 // other XCDs load: 96x96x8 nb 16 step 54.0 | 58.0 at best.  Below 2^21 numbers
-// the fewest chunks along w stay: TI c128 36x166x43 nb 2 plain 31.7 in three,
-// 37.6 in the four that would fill the round; 83x19x25 nb 8 20.6 and 22.8.
+// and with more than two workgroups per CU a round is not filled by more chunks:
+// TI c128 36x166x43 nb 2 plain 31.7 in three, 37.6 in four; 131x89x30 nb 1 24.0
+// in three, 25.3 in five.
 // nxs: column tiles per row.
 template <class P>
 StagedWalk staged_walk(const SweepParams& p, int nxs, int G8, bool full_walk) {
@@ -1544,11 +1545,11 @@ StagedWalk staged_walk(const SweepParams& p, int nxs, int G8, bool full_walk) {
         k.chunk(full_walk && p.st_C <= 0 ? k.nW : p.st_C, nxs, 1);
         return k;
     }
-    auto fill = [&](const StagedWalk& from, StagedWalk& best) {
+    auto fill = [&](const StagedWalk& from, int least, StagedWalk& best) {
         for (int nwc = 1; nwc <= 8; ++nwc) {
             StagedWalk t = from;
             t.chunk((t.nW + nwc - 1) / nwc, nxs, G8);
-            if (t.cost < best.cost) best = t;
+            if (t.C >= least && t.cost < best.cost) best = t;
         }
     };
     const int cols = k.nm * nxs, n0 = std::max(1, std::min((G8 + cols - 1) / cols, k.nW));
@@ -1556,8 +1557,9 @@ StagedWalk staged_walk(const SweepParams& p, int nxs, int G8, bool full_walk) {
     if (p.st_Bm <= 0 && p.st_G8 <= 0) {
         const StagedWalk k0 = k;
         k.cost *= 0.92;
-        if (p.L[0] * Ly * Lz * P::NO * p.nb >= (int64_t(1) << 21)) fill(k0, k);
-        if (walks_either<P>() && Lz < 8) fill(StagedWalk(Lz, Ly, nxs, 1), k);
+        const bool more = G8 <= 64 || p.L[0] * Ly * Lz * P::NO * p.nb >= (int64_t(1) << 21);
+        fill(k0, more ? 1 : k0.C, k);
+        if (walks_either<P>() && Lz < 8) fill(StagedWalk(Lz, Ly, nxs, 1), 1, k);
     }
     return k;
 }

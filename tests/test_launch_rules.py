@@ -68,6 +68,8 @@ WALKS = [
     ("weyl 1 130 130 60 4 128", (20, 0)),     # 20 planes 42.8, 12 planes 47.2
     ("weyl 1 100 90 40 8 128", (14, 0)),      # 14 planes 30.4, 8 planes 35.5
     ("ti 0 36 166 43 2 96", (15, 0)),         # 15 planes 31.7, 11 planes 37.6
+    ("weyl 0 10 118 74 8 96", (13, 0)),       # fewer chunks fill it: 13 planes 24.4, 11 planes 26.2
+    ("ti 0 40 40 40 8 64", (8, 0)),           # adjoint steps: more chunks gain, gradient 1383 against 1510 in 14
     ("ti 1 57 83 46 8 96", (23, 0)),          # series steps: 23 planes 62.1, 46 planes 66.3
     ("ti 0 240 240 6 32 64", (30, 1)),        # along y 346, along z 402
 ]
