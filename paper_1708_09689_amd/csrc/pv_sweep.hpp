@@ -1644,10 +1644,6 @@ hipError_t launch_staged(SweepParams& p, int num_cus, hipStream_t s) {
     return launch_staged_w<P, T, VT, E, EPM, NT, 1>(p, num_cus, s);
 }
 
-// Epilogue specialisations of the staged kernel: the Chebyshev step with
-// fused dots (KPM), the series step (propagation, filters), the plain sweep
-// or Chebyshev step without dots (with gamma = 0: no z stream at all), and
-// every other combination with the flags read at run time.
 // Whether a launch is the adjoint step of a gradient with everything that the
 // staged kernel reads a step ahead: all three sources, in 16-byte elements.
 // Bound by its 6 vector streams; the direct kernel also re-reads its neighbours
@@ -1660,6 +1656,10 @@ bool staged_adjoint(const SweepParams& p) {
     return p.gw[0] && p.gw[1] && p.gw[2] && (all & 15) == 0;
 }
 
+// Epilogue specialisations of the staged kernel: the Chebyshev step with
+// fused dots (KPM), the series step (propagation, filters), the plain sweep
+// or Chebyshev step without dots (with gamma = 0: no z stream at all), and
+// every other combination with the flags read at run time.
 template <class P, typename T, typename VT, int E>
 hipError_t launch_staged_ep(SweepParams& p, int nt, int num_cus, hipStream_t s) {
     constexpr unsigned KPM = EP_STORE_Y | EP_MOMENTS, DOTS = EP_STORE_Y | EP_DOTS, SERIES = EP_SERIES,
@@ -1682,9 +1682,6 @@ hipError_t launch_staged_ep(SweepParams& p, int nt, int num_cus, hipStream_t s) 
             return p.gamma == 0.0 ? launch_staged<P, T, VT, E, PLAIN | EP_NO_Z>(p, num_cus, s)
                                   : launch_staged<P, T, VT, E, PLAIN>(p, num_cus, s);
     }
-    if constexpr (sizeof(T) == 8 && E == 1 && P::FAMILY != FAM_GENERIC) {
-        if (staged_adjoint<P, T>(p)) return launch_staged<P, T, VT, 1, EP_ADJOINT>(p, num_cus, s);
-    }
     if constexpr (sizeof(T) == 8 && E == 2) {
         // the run-time epilogue at two complex128 elements per lane needs more
         // than 256 VGPRs: one element per lane, default walk and workgroups
@@ -1700,7 +1697,7 @@ hipError_t launch_staged_ep(SweepParams& p, int nt, int num_cus, hipStream_t s) 
 
 // Epilogues the staged kernel takes by default: plain sweeps, the Chebyshev
 // step with dots and the series steps; adjoint steps with all three sources
-// where launch_typed says so, other adjoint epilogues take the direct kernel,
+// where adjoint_default says so, other adjoint epilogues take the direct kernel,
 // which issues their loads together with the neighbour loads.
 // Small blocks (below 2^20 elements, cache resident) are launch-latency
 // bound, where the direct kernel's single pass beats the staged walks.
@@ -1708,6 +1705,16 @@ bool large_block(const SweepParams& p) {
     return p.L[0] * p.L[1] * p.L[2] * p.n_orb * p.nb >= (int64_t(1) << 20);
 }
 bool staged_default(const SweepParams& p) { return (p.ep & (EP_GTERMS | EP_GRAD)) == 0 && large_block(p); }
+
+// Adjoint steps with all three sources that are staged by default: on large
+// blocks.  Weyl steps stay direct unless asked for: their few neighbours cost
+// little there, and ragged rows more here (gradients of 32 moments, direct |
+// staged: 64^3 nb 16 4272 | 4194, 100x90x40 nb 2 1182 | 1099, nb 8 3478 | 3759,
+// nb 32 13203 | 13327).
+template <class P>
+bool adjoint_default(const SweepParams& p) {
+    return P::FAMILY != FAM_WEYL && large_block(p);
+}
 
 // Elements per lane of a staged launch that asks for none: one for complex128,
 // two for complex64 (one 16-byte chunk per lane and row either way).
@@ -1796,42 +1803,57 @@ struct Tag {
 // the block is 16-byte aligned (its chunk loads); else the direct kernel.
 // p.kernel (or PV_SWEEP) 1 forces direct, 2 staged; p.st_E (or PV_STAGED_E)
 // selects the elements per lane.
+enum class Route { DIRECT, STAGED, STAGED_ADJOINT };
+template <class P, typename T>
+Route sweep_route(const SweepParams& p) {
+    static const int env_kernel = env_int("PV_SWEEP", 0);
+    const int kind = p.kernel > 0 ? p.kernel : env_kernel;
+    const bool aligned = ((reinterpret_cast<uintptr_t>(p.x) | reinterpret_cast<uintptr_t>(p.zero_row)) & 15) == 0;
+    // generic stencils default to staged only on 3D lattices (walks along z)
+    const bool can = P::FAMILY != FAM_GENERIC || p.generic_stageable;
+    const bool adjoint = staged_adjoint<P, T>(p);
+    const bool dflt = (staged_default(p) || (adjoint && adjoint_default<P>(p))) &&
+                      (P::FAMILY != FAM_GENERIC || p.L[2] > 1);
+    // a site must be whole 16-byte chunks: ring rows start one site
+    // before the tile and wrap by whole chunks (complex64 with
+    // n_orb * nb = 1 is half a chunk per site: direct kernel)
+    const bool whole = (P::NO * p.nb * int(sizeof(cplx<T>))) % 16 == 0;
+    if (!can || !aligned || !whole || P::NO * p.nb > STAGED_MAX_SITE || kind == 1 || (kind == 0 && !dflt))
+        return Route::DIRECT;
+    return adjoint ? Route::STAGED_ADJOINT : Route::STAGED;
+}
+
 template <class P, typename T, typename VT>
 hipError_t launch_typed(SweepParams& p, int num_cus, hipStream_t s) {
-    {
-        static const int env_kernel = env_int("PV_SWEEP", 0);
-        const int kind = p.kernel > 0 ? p.kernel : env_kernel;
-        const bool aligned = ((reinterpret_cast<uintptr_t>(p.x) | reinterpret_cast<uintptr_t>(p.zero_row)) & 15) == 0;
-        // generic stencils default to staged only on 3D lattices (walks along z)
-        const bool can = P::FAMILY != FAM_GENERIC || p.generic_stageable;
-        // Weyl adjoint steps stay direct unless asked for: their few neighbours
-        // cost little there, and ragged rows more here (gradient at 64^3 nb 16
-        // 4.66 ms direct, 4.24 staged; 100x90x40 nb 8 4.65 and 4.88)
-        const bool adj = P::FAMILY != FAM_WEYL && staged_adjoint<P, T>(p) && large_block(p);
-        const bool dflt = (staged_default(p) || adj) &&
-                          (P::FAMILY != FAM_GENERIC || p.L[2] > 1);
-        // a site must be whole 16-byte chunks: ring rows start one site
-        // before the tile and wrap by whole chunks (complex64 with
-        // n_orb * nb = 1 is half a chunk per site: direct kernel)
-        const bool whole = (P::NO * p.nb * int(sizeof(cplx<T>))) % 16 == 0;
-        if (can && aligned && whole && P::NO * p.nb <= STAGED_MAX_SITE && (kind == 2 || (kind == 0 && dflt))) {
-            const auto [e, nt] = staged_tile<P, T>(p, num_cus);
-            auto staged = [&, e = e, nt = nt](auto pt) -> hipError_t {
-                using Q = typename decltype(pt)::type;
-                if constexpr (sizeof(T) == 8)
-                    return e == 2 ? launch_staged_ep<Q, T, VT, 2>(p, nt, num_cus, s)
-                                  : launch_staged_ep<Q, T, VT, 1>(p, nt, num_cus, s);
-                else
-                    return e == 4 ? launch_staged_ep<Q, T, VT, 4>(p, nt, num_cus, s)
-                                  : launch_staged_ep<Q, T, VT, 2>(p, nt, num_cus, s);
-            };
-            if constexpr (P::FAMILY == FAM_GENERIC) {
-                if (p.generic_side_halo) return staged(Tag<PatGeneric<P::NO, true>>{});
-            }
-            return staged(Tag<P>{});
+    const Route route = sweep_route<P, T>(p);
+    if constexpr (sizeof(T) == 8 && P::FAMILY != FAM_GENERIC) {
+        // one number per lane whatever the shape says: the six vectors of a
+        // second one do not fit the registers (a longer tile's walk and
+        // workgroups are not this one's)
+        if (route == Route::STAGED_ADJOINT) {
+            SweepParams q = p;
+            if (staged_elems(p) != 1) q.st_C = q.st_Bm = q.st_G8 = 0;
+            const hipError_t e = launch_staged<P, T, VT, 1, EP_ADJOINT>(q, num_cus, s);
+            p.grid = q.grid;
+            return e;
         }
     }
-    (void)num_cus;
+    if (route != Route::DIRECT) {
+        const auto [e, nt] = staged_tile<P, T>(p, num_cus);
+        auto staged = [&, e = e, nt = nt](auto pt) -> hipError_t {
+            using Q = typename decltype(pt)::type;
+            if constexpr (sizeof(T) == 8)
+                return e == 2 ? launch_staged_ep<Q, T, VT, 2>(p, nt, num_cus, s)
+                              : launch_staged_ep<Q, T, VT, 1>(p, nt, num_cus, s);
+            else
+                return e == 4 ? launch_staged_ep<Q, T, VT, 4>(p, nt, num_cus, s)
+                              : launch_staged_ep<Q, T, VT, 2>(p, nt, num_cus, s);
+        };
+        if constexpr (P::FAMILY == FAM_GENERIC) {
+            if (p.generic_side_halo) return staged(Tag<PatGeneric<P::NO, true>>{});
+        }
+        return staged(Tag<P>{});
+    }
     KArgs<T, VT> a;
     make_kargs<P, T, VT>(p, false, a);
     p.grid = int(8 * ((a.ntiles + a.tpb - 1) / a.tpb));

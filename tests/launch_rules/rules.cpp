@@ -3,6 +3,8 @@
 //   tile FAMILY DTYPE Lx Ly Lz NB EPILOGUE   ->   elements per lane, lanes
 //   walk FAMILY DTYPE Lx Ly Lz NB GROUPS     ->   planes per walk, 1 along y
 //                                                 (short tile, workgroups per XCD)
+//   adjoint FAMILY DTYPE Lx Ly Lz NB KERNEL ELEMS -> 0 direct, 1 staged with the
+//                                                 run-time epilogue, 2 with its own
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -20,6 +22,11 @@ template <class P>
 pv::StagedWalk walk(const pv::SweepParams& p, int G8) {
     const int TW = p.dtype == 0 ? 256 : 512, rowel = int(p.L[0]) * P::NO * p.nb;
     return pv::staged_walk<P>(p, (rowel + TW - 1) / TW, G8, false);
+}
+
+template <class P>
+int adjoint(const pv::SweepParams& p) {
+    return int(p.dtype == 0 ? pv::sweep_route<P, double>(p) : pv::sweep_route<P, float>(p));
 }
 
 }  // namespace
@@ -49,6 +56,18 @@ int main() {
             const std::string n = name;
             const pv::StagedWalk w = n == "ti" ? walk<pv::PatTI>(p, G8) : walk<pv::PatWeyl>(p, G8);
             std::printf("%d %d\n", w.C, w.along_y);
+        } else if (std::strcmp(what, "adjoint") == 0) {
+            pv::SweepParams p{};
+            long L[3];
+            if (std::scanf("%d %ld %ld %ld %d %d %d", &p.dtype, &L[0], &L[1], &L[2], &p.nb, &p.kernel, &p.st_E) != 7) return 1;
+            for (int k = 0; k < 3; ++k) p.L[k] = L[k];
+            p.ep = pv::EP_ADJOINT;
+            p.z = p.gw[0] = p.gw[1] = p.gw[2] = reinterpret_cast<const void*>(uintptr_t(4096));
+            const std::string n = name;
+            p.n_orb = n == "ti" || n == "graphene4" ? 4 : 2;
+            std::printf("%d\n", n == "ti" ? adjoint<pv::PatTI>(p)
+                              : n == "weyl" ? adjoint<pv::PatWeyl>(p)
+                              : n == "graphene4" ? adjoint<pv::PatGraphene4>(p) : adjoint<pv::PatGraphene2>(p));
         } else {
             return 1;
         }

@@ -78,3 +78,18 @@ WALKS = [
 @pytest.mark.parametrize("launch,choice", WALKS)
 def test_walks_of_a_staged_launch(rules, launch, choice):
     assert rules("walk " + launch) == choice
+
+
+# adjoint steps: kernel and elements per lane of the launch shape -> 0 direct, 1
+# staged with the run-time epilogue (slower than direct), 2 with its own
+ADJOINTS = [
+    ("ti 0 64 64 64 8 0 0", 2), ("ti 0 64 64 64 8 0 2", 2), ("ti 0 64 64 64 8 2 1", 2), ("ti 0 64 64 64 8 2 2", 2),
+    ("ti 0 64 64 64 8 1 2", 0), ("ti 0 16 16 16 8 0 2", 0), ("ti 0 16 16 16 8 2 2", 2),
+    ("weyl 0 64 64 64 16 0 2", 0), ("weyl 0 64 64 64 16 2 2", 2), ("graphene4 0 512 512 1 8 0 2", 2),
+    ("ti 1 64 64 64 8 0 4", 0), ("ti 1 64 64 64 8 2 4", 1),
+]
+
+
+@pytest.mark.parametrize("launch,route", ADJOINTS)
+def test_route_of_an_adjoint_step(rules, launch, route):
+    assert rules("adjoint " + launch) == (route,)
