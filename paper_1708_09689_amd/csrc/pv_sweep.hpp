@@ -1707,13 +1707,20 @@ bool large_block(const SweepParams& p) {
 bool staged_default(const SweepParams& p) { return (p.ep & (EP_GTERMS | EP_GRAD)) == 0 && large_block(p); }
 
 // Adjoint steps with all three sources that are staged by default: on large
-// blocks.  Weyl steps stay direct unless asked for: their few neighbours cost
-// little there, and ragged rows more here (gradients of 32 moments, direct |
-// staged: 64^3 nb 16 4272 | 4194, 100x90x40 nb 2 1182 | 1099, nb 8 3478 | 3759,
-// nb 32 13203 | 13327).
+// blocks whose rows fill enough of the 256-number tiles (empty lanes load what
+// the direct kernel does not).  Gradients of 32 moments, all direct | adjoint
+// steps staged (us), with the fill of the tiles: TI 12x100x100 nb 4 (0.75)
+// 1567 | 1259, 17x300x60 nb 4 (0.53) 3773 | 3525, 3x300x300 nb 8 (0.38) 7739 |
+// 9125, 6x191x115 nb 2 (0.19) 1706 | 1926; in 2D, without side rows, graphene-2
+// 30x20000 nb 1 (0.23) 1086 | 1034, 8x80000 nb 1 (0.06) 2828 | 2919.  Weyl steps
+// stay direct unless asked for: their few neighbours cost little there, and
+// ragged rows more here (direct | staged: 64^3 nb 16 4272 | 4194, 100x90x40
+// nb 2 1182 | 1099, nb 8 3478 | 3759, nb 32 13203 | 13327).
 template <class P>
 bool adjoint_default(const SweepParams& p) {
-    return P::FAMILY != FAM_WEYL && large_block(p);
+    if (P::FAMILY == FAM_WEYL || !large_block(p)) return false;
+    const int64_t rowel = p.L[0] * P::NO * p.nb, tiles = (rowel + kBlock - 1) / kBlock * kBlock;
+    return P::DIM == 3 ? 2 * rowel >= tiles : 5 * rowel >= tiles;
 }
 
 // Elements per lane of a staged launch that asks for none: one for complex128,

@@ -86,6 +86,9 @@ ADJOINTS = [
     ("ti 0 64 64 64 8 0 0", 2), ("ti 0 64 64 64 8 0 2", 2), ("ti 0 64 64 64 8 2 1", 2), ("ti 0 64 64 64 8 2 2", 2),
     ("ti 0 64 64 64 8 1 2", 0), ("ti 0 16 16 16 8 0 2", 0), ("ti 0 16 16 16 8 2 2", 2),
     ("weyl 0 64 64 64 16 0 2", 0), ("weyl 0 64 64 64 16 2 2", 2), ("graphene4 0 512 512 1 8 0 2", 2),
+    # rows that leave the tiles mostly empty: direct by default
+    ("ti 0 3 300 300 8 0 0", 0), ("ti 0 6 191 115 2 0 0", 0), ("ti 0 17 300 60 4 0 0", 2), ("ti 0 12 100 100 4 0 0", 2),
+    ("graphene2 0 8 80000 1 1 0 0", 0), ("graphene2 0 30 20000 1 1 0 0", 2), ("ti 0 6 191 115 2 2 0", 2),
     ("ti 1 64 64 64 8 0 4", 0), ("ti 1 64 64 64 8 2 4", 1),
 ]
 
