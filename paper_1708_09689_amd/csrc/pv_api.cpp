@@ -2502,21 +2502,20 @@ bool batch_codegen(const pv_batch* B) {
     return true;
 }
 
-// Elements per lane of a staged batch whose shape leaves them open: the longer
-// tile where every CU still gets six walks of it (built-in families; walks are
-// whole columns, so nothing else balances the launch).  us per step, short |
-// long: TI c64 nb 16 64^3 x 12 (3072 walks) 975 | 912, c128 nb 8 32^3 x 64
-// (4096) 670 | 633; c64 nb 4 96^3 x 4 (768) 321 | 377.
-int batch_elems(const pv_batch* B, int dtype, int nb) {
-    const int longer = dtype == PV_C128 ? 2 : 4;
-    if (B->family == pv::FAM_GENERIC) return 0;
-    int64_t walks = 0;
+std::vector<pv::BatchRows> batch_rows(const pv_batch* B, int nb) {
+    std::vector<pv::BatchRows> rows;
     for (const pv_lattice* l : B->lats) {
-        const int64_t nxs = (l->L[0] * l->n_orb * nb + 256 * longer - 1) / (256 * longer);
-        const int64_t nm = l->dim == 3 ? (l->L[1] >= 8 ? (l->L[1] + 7) / 8 : l->L[1]) : 1;
-        walks += 8 * nm * nxs;
+        const int64_t Lm = l->dim == 3 ? l->L[1] : 1, Lw = l->L[l->dim - 1];
+        const bool split_m = Lm >= 8;   // else the outer axis is in eighths
+        rows.push_back({l->L[0] * l->n_orb * nb, split_m ? (Lm + 7) / 8 : Lm, split_m ? Lw : (Lw + 7) / 8, l->n_rows * nb});
     }
-    return walks >= 6 * 256 ? longer : 0;
+    return rows;
+}
+
+// Elements per lane of a staged batch whose shape leaves them open.
+int batch_elems(const pv_batch* B, int dtype, int nb) {
+    if (B->family == pv::FAM_GENERIC || !pv::batch_long_tile(batch_rows(B, nb), dtype == PV_C128)) return 0;
+    return dtype == PV_C128 ? 2 : 4;
 }
 
 // Launch description of instance i of a batch (every instance takes the
@@ -2532,27 +2531,15 @@ pv::SweepParams batch_params(const pv_batch* B, int i, int dtype, int nb, int el
     return p;
 }
 
-// The staged kernel serves a batch unless its shape asks for the direct one; by
-// default only batches of at least 72 * 1024 elements for each plane of the
-// longest walk: a walk takes about 1.3 us per plane however little runs beside
-// it, the direct kernel 18 (complex64) to 25 us per 2^20 elements.  us per step,
-// TI, direct | staged: c64 nb 4 24^3 x 3 (27 * 1024) 17.6 | 29.9, 24^3 x 8 (72 *
-// 1024) 41.5 | 34.6, nb 8 24^3 x 8 61.5 | 41.7, nb 1 32^3 x 64 234 | 146;
-// c128 nb 8 16^3 x 16 (128 * 1024) 52 | 33; nb 1, 20 to 56 cubed (42 * 1024) 75 | 79.
+// The staged kernel serves a batch unless its shape asks for the direct one (by
+// default where batch_stages says so).
 bool batch_may_stage(const pv_batch* B, int dtype, int nb) {
     static const char* env = std::getenv("PV_SWEEP");
     if ((B->family == pv::FAM_GENERIC && !batch_codegen(B)) || (env && std::atoi(env) == 1)) return false;
     if (B->n_orb * nb > pv::STAGED_MAX_SITE) return false;
     const int kind = batch_shape(B, dtype, nb).kernel;
     if (kind != 0 || (env && std::atoi(env) == 2)) return kind != 1;
-    int64_t elems = 0, planes = 1;
-    for (const pv_lattice* l : B->lats) {
-        elems += l->n_rows * nb;
-        const bool parts = l->dim == 2 || l->L[1] < 8;   // the outer axis in eighths
-        const int64_t Lw = l->L[l->dim - 1];
-        planes = std::max(planes, parts ? (Lw + 7) / 8 : Lw);
-    }
-    return elems >= planes * 72 * 1024;
+    return pv::batch_stages(batch_rows(B, nb), dtype == PV_C128);
 }
 
 pv_status batch_counts(const pv_batch* B, int dtype, int nb, int staged, std::vector<int>& nblocks, int& total) {

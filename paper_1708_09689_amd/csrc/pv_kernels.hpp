@@ -5,8 +5,10 @@
 #ifndef PV_RTC
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
+#include <vector>
 #else
 // run-time compiled kernels: the fixed-width integers of the RTC runtime header
 using __hip_internal::int64_t;
@@ -221,6 +223,51 @@ hipError_t launch_random_block(int dtype, int kind, int64_t n, uint64_t seed, ui
 // instance's workgroup count.  launch_batch_sweep takes the launch
 // description of any instance (family, types, nb, tuning, epilogue).
 size_t batch_record_bytes();
+
+// What the rules of a batch's default shape read of an instance: numbers per
+// row, middle rows of an XCD part, planes of a walk, numbers in all.
+struct BatchRows {
+    int64_t rowel, nm, planes, elems;
+};
+
+// Whether a staged batch takes the longer tile (512 complex128, 1024 complex64
+// numbers): where every CU still gets six walks of it and rows fill it nearly
+// as well (at most a tenth more numbers, padding included; walks are whole
+// columns, so nothing else balances the launch).  Over 86 batches the choice is
+// within 4% of the better tile where six walks are there.  us per step of TI,
+// short | long: c64 nb 16 64^3 x 12 (3072 walks, padding 1) 957 | 872, c128 nb 8
+// 32^3 x 64 (4096, 1) 667 | 609, nb 8 65^3 x 8 (2880, 1.11) 779 | 777, nb 2 65^3
+// x 16 (2304, 1.33) 501 | 565, c64 nb 4 32^3 x 64 (2048, 2) 184 | 253, nb 1 32^3
+// x 64 (2048, 2) 143 | 235, nb 4 96^3 x 4 (768, 1.33) 315 | 371; left out: c64
+// nb 4 128^3 x 2 (512 walks, one round) 399 | 286.
+inline bool batch_long_tile(const std::vector<BatchRows>& rows, bool c128) {
+    const int64_t tile = c128 ? 256 : 512;
+    int64_t walks = 0, fill_short = 0, fill_long = 0;
+    for (const BatchRows& r : rows) {
+        const int64_t ns = (r.rowel + tile - 1) / tile, nl = (r.rowel + 2 * tile - 1) / (2 * tile);
+        walks += 8 * r.nm * nl;
+        fill_short += r.nm * r.planes * ns * tile;
+        fill_long += r.nm * r.planes * nl * 2 * tile;
+    }
+    return walks >= 6 * 256 && 10 * fill_long <= 11 * fill_short;
+}
+
+// Whether a batch is staged by default: from 52 * 1024 complex128 or 72 * 1024
+// complex64 numbers for each plane of the longest walk.  A walk takes 1.1 to 1.6
+// us per plane however little runs beside it, the direct kernel 33 us per 2^20
+// complex128 numbers and 24 complex64 (more on many small lattices).  us per step
+// of TI, direct | staged (thousands per plane): c128 nb 1 64^3 x 3 (48) 78 | 86,
+// nb 2 56^3 x 2 (49) 78 | 76, nb 1 27, 62, 71 and 85 cubed (57) 179 | 119, nb 4
+// 45^3 x 2 (63) 76 | 67; c64 nb 1 80^3 x 2 (50) 109 | 106, 128^3 (64) 92 | 169,
+// nb 2 56^3 x 3 (74) 81 | 79, nb 4 40^3 x 4 (100) 80 | 62.
+inline bool batch_stages(const std::vector<BatchRows>& rows, bool c128) {
+    int64_t elems = 0, planes = 1;
+    for (const BatchRows& r : rows) {
+        elems += r.elems;
+        planes = std::max(planes, r.planes);
+    }
+    return elems >= planes * (c128 ? 52 : 72) * 1024;
+}
 // dst = 0 (bytes a multiple of 4)
 hipError_t launch_zero(void* dst, size_t bytes, hipStream_t s);
 hipError_t batch_fill_record(const SweepParams& p, int staged, void* dst, int* nblocks);

@@ -5,6 +5,8 @@
 //                                                 (short tile, workgroups per XCD)
 //   adjoint FAMILY DTYPE Lx Ly Lz NB KERNEL ELEMS -> 0 direct, 1 staged with the
 //                                                 run-time epilogue, 2 with its own
+//   batch NORB DTYPE NB LENGTHS... 0              -> 1 staged, 1 the longer tile
+//                                                 (cubes of the lengths)
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -68,6 +70,14 @@ int main() {
             std::printf("%d\n", n == "ti" ? adjoint<pv::PatTI>(p)
                               : n == "weyl" ? adjoint<pv::PatWeyl>(p)
                               : n == "graphene4" ? adjoint<pv::PatGraphene4>(p) : adjoint<pv::PatGraphene2>(p));
+        } else if (std::strcmp(what, "batch") == 0) {
+            const int no = std::stoi(name);
+            int dtype, nb;
+            long L;
+            std::vector<pv::BatchRows> rows;
+            if (std::scanf("%d %d", &dtype, &nb) != 2) return 1;
+            while (std::scanf("%ld", &L) == 1 && L) rows.push_back({L * no * nb, (L + 7) / 8, L, L * L * L * no * nb});
+            std::printf("%d %d\n", int(pv::batch_stages(rows, dtype == 0)), int(pv::batch_long_tile(rows, dtype == 0)));
         } else {
             return 1;
         }

@@ -96,3 +96,28 @@ ADJOINTS = [
 @pytest.mark.parametrize("launch,route", ADJOINTS)
 def test_route_of_an_adjoint_step(rules, launch, route):
     assert rules("adjoint " + launch) == (route,)
+
+
+# batches of cubes: (staged, longer tile)
+BATCHES = [
+    ((4, 1, 16), [64] * 12, (1, 1)),            # short 957, long 872
+    ((4, 0, 8), [32] * 64, (1, 1)),             # 667, 609
+    ((4, 1, 4), [32] * 64, (1, 0)),             # 184, 253: rows of half a long tile
+    ((4, 1, 1), [32] * 64, (1, 0)),             # 143, 235
+    ((4, 1, 4), [65] * 16, (1, 0)),             # 509, 586
+    ((4, 1, 8), [33] * 40, (1, 0)),             # 371, 423
+    ((4, 0, 2), [65] * 16, (1, 0)),             # 501, 565
+    ((4, 1, 4), [96] * 4, (1, 0)),              # 315, 371: too few walks
+    ((2, 1, 1), [95] * 27, (1, 0)),             # 534, 869
+    ((4, 0, 1), [27, 62, 71, 85], (1, 0)),      # direct 179, staged 119
+    ((4, 0, 4), [45] * 2, (1, 0)),              # direct 76, staged 67
+    ((4, 0, 1), [64] * 3, (0, 0)),              # direct 78, staged 86
+    ((4, 0, 1), [96], (0, 0)),                  # direct 77, staged 121
+    ((4, 1, 1), [128], (0, 0)),                 # direct 92, staged 169
+]
+
+
+@pytest.mark.parametrize("kind,lengths,choice", BATCHES)
+def test_default_shape_of_a_batch(rules, kind, lengths, choice):
+    line = "batch {} {} {} ".format(*kind) + " ".join(map(str, lengths)) + " 0"
+    assert rules(line) == choice
