@@ -188,6 +188,29 @@ hipError_t launch_block_rotate(int dtype, int64_t rows, int bw, int nin, int nou
                                const double* Q, void* OUT, int64_t out_stride, hipStream_t s);
 hipError_t launch_rotate(int dtype, int64_t rows, int nx, int ny, const void* X, const double* Q,
                          int accumulate, void* Y, hipStream_t s);
+// Whether launch_rotate takes one thread per entry instead of the matrix
+// instructions, which pad both sides of a narrow product to 16 columns and start
+// with an LDS fill and a barrier.  us per call in a graph, entries | matrix
+// instructions, accumulating complex128 (complex64 alike):
+//   rows        1x1         4x4         8x1         8x8         16x2        32x32
+//   3000        2.0 | 3.2   2.3 | 3.4   3.0 | 3.6   2.8 | 3.7   3.3 | 3.9   6.0 | 5.7
+//   30000       2.2 | 3.6   2.7 | 3.9   3.1 | 4.2   4.2 | 4.6   3.6 | 4.6   34 | 13
+//   200000      2.7 | 8.5   6.5 | 9.7   9.0 | 11    22 | 17     20 | 16     184 | 52
+// So always for few columns (at 600000 rows 1x1 still 4.9 times, 4x4 1.4 times as
+// fast), and for more of them on blocks so small that latency decides; longer
+// where the old Y is read too or numbers are half as long (8x4 at 200000 rows:
+// 12.5 | 15.3 accumulating, 10.6 | 9.1 not).
+inline bool rotate_by_entry(int dtype, int64_t rows, int nx, int ny, bool accumulate) {
+    const int64_t work = rows * nx * ny;
+    const bool c128 = dtype == 0;
+    if (nx == 1) return ny <= 16 || rows <= 200000 || (!c128 && accumulate);
+    if (nx <= 8) {
+        if (nx * ny <= 16 && (nx <= 4 || !c128)) return true;
+        if (ny <= 4 && (accumulate || !c128)) return work <= (ny == 1 ? 2000000 : 7000000);
+        return work <= 1200000;
+    }
+    return nx <= 24 && ny >= 2 && ny <= 4 && work <= 3000000;
+}
 hipError_t launch_copy(const void* src, void* dst, size_t bytes, hipStream_t s);
 hipError_t launch_triad(const void* x, const void* z, void* y, size_t bytes, hipStream_t s);
 // workgroups of the read probe (its sink holds one 32-bit word per wave)

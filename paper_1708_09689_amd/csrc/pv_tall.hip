@@ -2,7 +2,8 @@
 // Y = X Q (rotation), and the same over a search space kept as column blocks
 // (Sec. 4.2: orthonormalisation and Rayleigh-Ritz of filter diagonalisation).
 //
-// Both are streams of one pass over the blocks: at 32 x 32 columns a row
+// Narrow rotations of pv_block_rotate take one thread per entry
+// (rotate_by_entry).  Otherwise both are streams of one pass over the blocks: at 32 x 32 columns a row
 // costs 1 KiB of reads (180 ps at 5.8 TB/s) and 8192 flops (120 ps at the
 // 68 TFLOP/s an FP64 library product reaches), so the target is the memory
 // rate, and above 48 columns or so the matrix rate.  v_mfma_f64_16x16x4
@@ -375,6 +376,33 @@ __global__ __launch_bounds__(NW * 64, LQ ? 4 : 3) void rotate_mfma_kernel(Cols<T
     }
 }
 
+// The same for few columns, one thread per entry of Y: bound by latency on
+// small blocks and by its reads, which the threads of a row share through L1, on
+// large ones (rotate_by_entry has the times).  The four real products have sums
+// of their own, as above.
+template <typename T>
+__global__ __launch_bounds__(kTallBlock) void rotate_entry_kernel(const T* __restrict__ X, const double* __restrict__ Q,
+                                                                  int64_t n, int nx, int ny, int accumulate,
+                                                                  T* __restrict__ Y) {
+    for (int64_t e = blockIdx.x * int64_t(kTallBlock) + threadIdx.x; e < n; e += int64_t(gridDim.x) * kTallBlock) {
+        const int64_t r = (e >> 32) == 0 ? int64_t(uint32_t(e) / uint32_t(ny)) : e / ny;
+        const int j = int(e - r * ny);
+        f64x2 y{0.0, 0.0};
+        if (accumulate) y = ld_c(static_cast<const T*>(Y), e);
+        double rr = 0.0, ii = 0.0, ri = 0.0, ir = 0.0;
+        for (int i = 0; i < nx; ++i) {
+            const f64x2 u = ld_c(X, r * nx + i);
+            const double qr = Q[(i * ny + j) * 2], qi = Q[(i * ny + j) * 2 + 1];
+            rr += u.x * qr;
+            ii += u.y * qi;
+            ri += u.x * qi;
+            ir += u.y * qr;
+        }
+        using V = T __attribute__((ext_vector_type(2)));
+        *reinterpret_cast<V*>(Y + 2 * e) = V{T(y.x + (rr - ii)), T(y.y + (ri + ir))};
+    }
+}
+
 template <typename T>
 Cols<T> cols(const void* base, int64_t stride, int ld, int n, int lg) {
     return Cols<T>{static_cast<const T*>(base), stride, ld, n, lg};
@@ -490,6 +518,15 @@ hipError_t launch_block_gram(int dtype, int64_t rows, int bw, int nblk, const vo
 
 hipError_t launch_rotate(int dtype, int64_t rows, int nx, int ny, const void* X, const double* Q, int accumulate,
                          void* Y, hipStream_t s) {
+    if (rotate_by_entry(dtype, rows, nx, ny, accumulate != 0)) {
+        const int64_t n = rows * ny, g = (n + kTallBlock - 1) / kTallBlock;
+        return by_type(dtype, [&](auto tt) -> hipError_t {
+            using T = decltype(tt);
+            hipLaunchKernelGGL((rotate_entry_kernel<T>), dim3(unsigned(g < 8192 ? g : 8192)), dim3(kTallBlock), 0, s,
+                               static_cast<const T*>(X), Q, n, nx, ny, accumulate, static_cast<T*>(Y));
+            return hipGetLastError();
+        });
+    }
     return rotate_any(dtype, rows, X, 0, nx, nx, 31, Q, accumulate, Y, 0, ny, ny, 31, s);
 }
 

@@ -7,6 +7,7 @@
 //                                                 run-time epilogue, 2 with its own
 //   batch NORB DTYPE NB LENGTHS... 0              -> 1 staged, 1 the longer tile
 //                                                 (cubes of the lengths)
+//   rotate DTYPE ROWS NX NY ACCUMULATE            -> 1 one thread per entry
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -70,6 +71,11 @@ int main() {
             std::printf("%d\n", n == "ti" ? adjoint<pv::PatTI>(p)
                               : n == "weyl" ? adjoint<pv::PatWeyl>(p)
                               : n == "graphene4" ? adjoint<pv::PatGraphene4>(p) : adjoint<pv::PatGraphene2>(p));
+        } else if (std::strcmp(what, "rotate") == 0) {
+            long rows;
+            int nx, ny, acc;
+            if (std::scanf("%ld %d %d %d", &rows, &nx, &ny, &acc) != 4) return 1;
+            std::printf("%d\n", int(pv::rotate_by_entry(std::stoi(name), rows, nx, ny, acc != 0)));
         } else if (std::strcmp(what, "batch") == 0) {
             const int no = std::stoi(name);
             int dtype, nb;

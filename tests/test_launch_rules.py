@@ -121,3 +121,28 @@ BATCHES = [
 def test_default_shape_of_a_batch(rules, kind, lengths, choice):
     line = "batch {} {} {} ".format(*kind) + " ".join(map(str, lengths)) + " 0"
     assert rules(line) == choice
+
+
+# rotations: one thread per entry (1) or matrix instructions (0)
+ROTATIONS = [
+    ("0 200000 1 1 0", 1),      # entries 2.4, matrix instructions 7.1
+    ("0 1400000 2 2 1", 1),     # 2.7 times as fast
+    ("1 1400000 8 1 0", 1),     # 1.7 times
+    ("0 1400000 8 1 0", 0),     # matrix instructions 1.6 times as fast
+    ("0 1400000 8 1 1", 0),     # 85, 69
+    ("0 200000 8 4 1", 1),      # 12.5, 15.3
+    ("1 600000 1 64 1", 1),     # 131, 164
+    ("0 600000 1 64 1", 0),     # matrix instructions 1.1 times as fast
+    ("0 3000 2 1 0", 1),        # 1.9, 2.6
+    ("0 30000 4 8 1", 1),       # 1.2 times
+    ("0 200000 8 8 0", 0),      # matrix instructions 1.9 times as fast
+    ("0 30000 16 2 1", 1),      # 3.4, 4.5
+    ("0 30000 16 1 1", 0),      # equal at this size, matrix instructions at others
+    ("0 30000 64 1 1", 0),      # 1.2 times as fast
+    ("0 1382400 32 32 1", 0),   # 396 against 1515
+]
+
+
+@pytest.mark.parametrize("launch,entry", ROTATIONS)
+def test_kernel_of_a_rotation(rules, launch, entry):
+    assert rules("rotate " + launch) == (entry,)
