@@ -24,6 +24,9 @@
 // for two waves spills: 12 us per step instead of 8.6 (four steps per pass).
 #include "pv_sweep.hpp"
 
+#include <algorithm>
+#include <cmath>
+
 namespace pv {
 namespace {
 
@@ -460,16 +463,49 @@ hipError_t plane_instance(int family, int dtype, int nb, int TS, F&& f) {
 
 }  // namespace
 
+namespace {
+
+// Times (us) of `steps` steps as passes of TS steps and as sweeps, fitted to 250
+// lattices of 4 KB to 100 MB per vector with 2 to 32 steps each (12% rms both).
+// A pass is bound by a wave's instructions per row, one or (where the registers
+// allow two) two rounds of workgroups at once, or by its memory; a sweep by its
+// launch, its streams, and the 256-number tiles that its rows leave empty.
+double plane_time(const SweepParams& p, int TS, int steps, bool kpm, double bytes) {
+    const bool g2 = p.family == FAM_GRAPHENE2, c128 = p.dtype == 0;
+    int ntx, C, nyc, grid;
+    plane_shape(p, TS, ntx, C, nyc, grid);
+    const double items = double((ntx + 3) / 4) * nyc, levels = C + 2 * TS;
+    // us per row of a wave
+    const double row = !g2 ? (c128 ? (kpm ? 1.11 : 1.46) : 1.17)
+                           : (c128 ? (TS == 6 ? (kpm ? 0.90 : 1.12) : (kpm ? 0.78 : 0.95)) : (TS == 6 ? 0.83 : 0.79));
+    const bool two = g2 && !(c128 && TS == 6);
+    const double rounds = two ? std::max(1.0, items / 512) : std::ceil(items / 256);
+    const double walk = rounds * (levels + 2.5) * row, mem = (kpm ? 5.8e-7 : 8.1e-7) * bytes * levels / C;
+    const int passes = (steps + TS - 1) / TS;
+    return passes * (0.9 + std::pow(std::pow(walk, 4) + std::pow(mem, 4), 0.25)) + (kpm ? 3.8 : 0.0);
+}
+double sweeps_time(const SweepParams& p, int steps, bool kpm, double bytes) {
+    const bool c128 = p.dtype == 0, large = bytes >= double(1 << 20) * (c128 ? 16 : 8);   // staged
+    const int64_t rowel = p.L[0] * p.n_orb * p.nb, tile = large && !c128 ? 512 : 256;
+    const double tiles = double((rowel + tile - 1) / tile * tile) * double(p.L[1]), part = double((p.L[1] + 7) / 8);
+    const double streams = (kpm ? 3.0 : 11.0 / 3.0) * (large ? (part + 1.3) / part : 1.0);
+    return steps * (4.0 + streams * bytes * 1.23e-7 + tiles * (large ? 2e-6 : 4e-6)) + (kpm ? 7.7 : 0.0);
+}
+
+}  // namespace
+
 // Which runs take passes.  Fields generated in the kernel and complex diagonals
 // are left out (registers), as are the moments of complex64 vectors (their FP64
 // dots keep the sweeps' rounding) and blocks of more than four columns, whose
-// halo would be most of a wave.  Measured per step, pass against the faster
-// sweep kernel in its best shape (us; graphene-2 / graphene-4 complex128
-// series, one column): 12 x 10 3.4 / 3.7 and 4.3 / 3.7, 200 x 150 3.6 / 4.5
-// and 5.3 / 5.5, 512 x 512 5.3 / 9.5 and 11.5 / 18.0, 2000 x 1500 22.7 / 82
-// and 98 / 174; four columns 512 x 512 12.3 / 31.9 and 31.9 / 53.5; moments
-// 12 x 10 3.0 / 4.7 and 3.7 / 5.0, 512 x 512 4.3 / 10.0 and 9.0 / 15.0.  So
-// only small four-orbital complex128 series stay with the sweeps.
+// halo would be most of a wave.  The others take them where they are estimated
+// to be faster: a last pass computes all of its levels, and lattices of few
+// sites along x leave most of a wave's lanes and of a workgroup's waves idle.
+// Measured (us, passes | sweeps): series of 32 terms, one complex128 column:
+// graphene-2 12x10 105 | 134, 512x512 167 | 279, 2000x1500 812 | 1954, 8x20000
+// 638 | 808; graphene-4 512x512 383 | 458, 8x20000 1277 | 858; of 4 terms 200x150
+// 30 | 21; moments, 8 steps: graphene-4 200x150 40 | 49, 8x20000 with four columns
+// 297 | 238.  Four-orbital complex128 series below 4 MiB per vector never gain
+// (32 terms, 60x1000 200 | 171, 16x512 with four columns 182 | 164).
 int plane_steps(const SweepParams& p, int steps, bool kpm) {
     const bool g2 = p.family == FAM_GRAPHENE2, g4 = p.family == FAM_GRAPHENE4;
     if (!(g2 || g4) || p.nb > 4 || p.kernel != 0 || !p.real_diag || p.field == 2 || steps < 2) return 0;
@@ -478,11 +514,13 @@ int plane_steps(const SweepParams& p, int steps, bool kpm) {
     if (p.L[1] < kPlaneMaxSteps + 2) return 0;
     const double bytes = double(p.L[0]) * double(p.L[1]) * p.n_orb * p.nb * (p.dtype == 0 ? 16 : 8);
     if (bytes >= 2147483648.0) return 0;   // 32-bit offsets of the buffers
-    if (g4 && !kpm && p.dtype == 0 && bytes < 65536.0 * 16) return 0;
-    if (g4) return p.dtype == 0 ? 3 : 4;
-    if (p.nb > 1) return 4;
-    auto cost = [&](int ts) { return ((steps + ts - 1) / ts) * (ts + 2.7); };
-    return cost(6) <= cost(4) ? 6 : 4;
+    if (g4 && !kpm && p.dtype == 0 && bytes < 4194304.0) return 0;   // the registers of one wave per SIMD
+    int ts = g4 && p.dtype == 0 ? 3 : 4;
+    if (g2 && p.nb == 1) {
+        auto cost = [&](int n) { return ((steps + n - 1) / n) * (n + 2.7); };
+        if (cost(6) <= cost(4)) ts = 6;
+    }
+    return 0.9 * plane_time(p, ts, steps, kpm, bytes) < sweeps_time(p, steps, kpm, bytes) ? ts : 0;
 }
 
 int plane_grid(const SweepParams& p, int TS) {
