@@ -75,12 +75,14 @@ __device__ __forceinline__ double lane_shift(double v, int nb) {
     return __hiloint2double(lane_shift<UP, ONE>(__double2hiint(v), nb), lane_shift<UP, ONE>(__double2loint(v), nb));
 }
 
-// Raw buffers over a whole vector: a lane offset of kNone, or any offset into
-// a buffer of length 0, loads zeros and stores nothing.  So lanes and rows
-// outside the lattice, halo lanes and absent operands need no branches, and
-// with no memory operation in a branch the compiler waits for exactly the
-// loads that an iteration uses.
-constexpr uint32_t kNone = 0xffffffffu;
+// Raw buffers over a whole vector (below 2 GiB): a lane offset of kNone, or any
+// offset into a buffer of length 0, loads zeros and stores nothing (2^31 is past
+// every length, and neither the words of a chunk nor a row's offset carry it
+// round to the start).  So lanes and rows
+// outside the lattice, halo lanes and absent operands need no branches, and with
+// no memory operation in a branch the compiler waits for exactly the loads that
+// an iteration uses.
+constexpr uint32_t kNone = 0x80000000u;
 using Rsrc = __amdgpu_buffer_rsrc_t;
 struct Row {
     Rsrc r;
