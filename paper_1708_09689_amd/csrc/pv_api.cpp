@@ -1019,13 +1019,15 @@ pv_status kpm_forward(pv_lattice* l, int dtype, int nb, int M, double a, double 
     const int64_t stride = int64_t(partial_bytes(l, nb) / sizeof(double));
     pv::SweepParams p = base_params(l, dtype, nb);
     if ((st = fill_traversal(l, dtype, nb, p)) != PV_OK) return st;
-    p.ep = pv::EP_STORE_Y | pv::EP_MOMENTS;
+    // generated kernels: one instance for these steps and for pv_spmmv with dots
+    const int width = p.cg_src ? 4 : 2;
+    p.ep = pv::EP_STORE_Y | (p.cg_src ? pv::EP_DOTS : pv::EP_MOMENTS);
     const double invD = 1.0 / double(l->n_rows);
     // first step not reduced yet, its buffer, rows of its partials (the steps
     // that read r may have another launch shape: r need not be aligned)
     int n0 = 0, buf0 = 0, grid0 = 0;
     auto reduce_before = [&](int n) -> hipError_t {
-        const hipError_t e = pv::launch_kpm_reduce(part + buf0 * stride, stride, grid0, nb, 2, n0, n - n0, mu, M, invD, s);
+        const hipError_t e = pv::launch_kpm_reduce(part + buf0 * stride, stride, grid0, nb, width, n0, n - n0, mu, M, invD, s);
         buf0 += n - n0;
         n0 = n;
         return e;
@@ -1757,10 +1759,11 @@ extern "C" pv_status pv_autotune(pv_lattice* l, int dtype, int nb, const char* c
                 p.eta_im = p.etax_im = p.etaz_im = 0.25;
                 if (hipError_t e = pv::launch_sweep(p, num_cus(), s); e != hipSuccess) return e;
             } else {
-                p.ep = pv::EP_STORE_Y | pv::EP_MOMENTS;
+                p.ep = pv::EP_STORE_Y | (p.cg_src ? pv::EP_DOTS : pv::EP_MOMENTS);   // as kpm_forward
                 p.partials = part;
                 hipError_t e = pv::launch_sweep(p, num_cus(), s);
-                if (e == hipSuccess) e = pv::launch_kpm_reduce(part, 0, p.grid, nb, 2, 0, 1, dots, 2, 1.0, s);
+                if (e == hipSuccess)
+                    e = pv::launch_kpm_reduce(part, 0, p.grid, nb, p.cg_src ? 4 : 2, 0, 1, dots, 2, 1.0, s);
                 if (e != hipSuccess) return e;
             }
         }
