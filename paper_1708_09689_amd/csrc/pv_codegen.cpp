@@ -266,8 +266,11 @@ hipError_t staged_go_w(SweepParams& p, int num_cus, hipStream_t s, unsigned epm)
 
 template <class P, typename T, typename VT, int E, int NT>
 hipError_t staged_go(SweepParams& p, int num_cus, hipStream_t s, unsigned epm) {
+    // two complex64 columns per element in every block of at least two, so that
+    // one instance serves them all: the kernel's 16-byte accesses to z, y and the
+    // accumulator need 8-byte alignment only (x is aligned in every staged launch)
     if constexpr (sizeof(T) == 4) {
-        if (epm != 0u && paired<T>(p)) return staged_go_w<P, T, VT, E, NT, 2>(p, num_cus, s, epm);
+        if (epm != 0u && p.nb >= 2) return staged_go_w<P, T, VT, E, NT, 2>(p, num_cus, s, epm);
     }
     return staged_go_w<P, T, VT, E, NT, 1>(p, num_cus, s, epm);
 }

@@ -689,9 +689,11 @@ __device__ __forceinline__ u32x4 ld_chunk(const void* base, uint32_t boff) {
     return *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(base) + boff);
 }
 
+// (of a vector that is aligned as its numbers are)
 template <typename T>
 __device__ __forceinline__ u32x4 ld_chunk_nt(const void* base, uint32_t boff) {
-    return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(base) + boff));
+    using V = unsigned int __attribute__((ext_vector_type(4), aligned(sizeof(cplx<T>))));
+    return __builtin_nontemporal_load(reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + boff));
 }
 
 // One step's worth of rows in flight: ring row with halo, z and acc_in
@@ -971,7 +973,7 @@ __device__ __forceinline__ void staged_epilogue(const KArgs<T, VT>& a, int64_t e
                                                 const Elem<T, W>& z, const Elem<T, W>& acc, const Elem<T, W>& h, T alT,
                                                 T gaT, T er, T ei, double (&dxx)[W], double (&dxr)[W],
                                                 double (&dxi)[W], double (&dyy)[W]) {
-    using V = T __attribute__((ext_vector_type(2 * W)));
+    using V = T __attribute__((ext_vector_type(2 * W), aligned(sizeof(cplx<T>))));
     V yo, ao;
 #pragma unroll
     for (int q = 0; q < W; ++q) {

@@ -47,3 +47,36 @@ def test_moments_and_sweeps_with_dots_share_an_instance(dtype):
     assert pv.pv_codegen_instances() == n0 + 1
     assert torch.equal(y, v) and torch.equal(d, e)   # the generated kernel ran without allocation
     assert (y - w).abs().max() < (1e-12 if dtype == torch.complex128 else 1e-5) * w.abs().max()
+
+
+@pytest.mark.parametrize("nb", [2, 8])
+def test_complex64_blocks_off_16_bytes_share_the_instances(nb):
+    """Same operations on every number whatever the alignment: equal bits, also
+    in place, with guards around the misaligned blocks."""
+    lat, x, z = fresh_lattice(110 + nb, torch.complex64, nb=nb)
+    n = x.numel()
+
+    def off(t, fill=7.0):
+        buf = torch.full((n + 4,), fill, dtype=t.dtype, device="cuda")
+        v = buf[1:1 + n].view(t.shape)
+        v.copy_(t)
+        assert v.data_ptr() % 16 == 8
+        return buf, v
+
+    for gamma, flags in ((-1.0, 7), (-1.0, 0), (0.0, 0)):
+        y = z.clone()
+        d = pv.pv_spmmv(lat, x, y, 0.5, 0.25, gamma, z=y if gamma else None, dot_flags=flags)
+        n0 = pv.pv_codegen_instances()
+        buf, w = off(z)
+        e = pv.pv_spmmv(lat, x, w, 0.5, 0.25, gamma, z=w if gamma else None, dot_flags=flags)
+        assert pv.pv_codegen_instances() == n0
+        assert torch.equal(y, w) and (not flags or torch.equal(d, e))
+        assert bool((buf[:1] == 7.0).all()) and bool((buf[1 + n:] == 7.0).all())
+    coef = np.array([0.5, 0.3 - 0.1j, 0.2j, -0.1, 0.05, 0.02, 0.1, -0.2, 0.03])
+    y = torch.empty_like(x)
+    pv.pv_cheb_series(lat, x, y, 9.0, 0.1, coef)
+    n0 = pv.pv_codegen_instances()
+    buf, w = off(x)
+    pv.pv_cheb_series(lat, x, w, 9.0, 0.1, coef)
+    assert pv.pv_codegen_instances() == n0 and torch.equal(y, w)
+    assert bool((buf[:1] == 7.0).all()) and bool((buf[1 + n:] == 7.0).all())
