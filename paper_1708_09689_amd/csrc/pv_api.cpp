@@ -1284,6 +1284,7 @@ pv_status series_sweeps(pv_lattice* l, int dtype, int nb, double a, double b, in
     pv_status st;
     if ((st = fill_traversal(l, dtype, nb, p)) != PV_OK) return st;
     p.beta = b;
+    p.cg_series = K >= 4;   // shorter ones have no later plain step
     for (int k = 1, first = 0; k <= K; ++k) {   // first: the first term not in acc yet
         const bool last = k == K;
         p.x = k == 1 ? X : wbuf(k - 1);

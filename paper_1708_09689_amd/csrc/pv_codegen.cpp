@@ -294,7 +294,7 @@ hipError_t staged_ep(SweepParams& p, int num_cus, hipStream_t s) {
         unsigned epm = 0u;
         if (p.ep == KPM || p.ep == DOTS) epm = p.ep;
         else if (p.ep == SERIES) epm = SERIES;
-        else if (p.ep == PLAIN) epm = p.gamma == 0.0 ? (PLAIN | EP_NO_Z) : PLAIN;
+        else if (p.ep == PLAIN) epm = p.gamma == 0.0 && !p.cg_series ? (PLAIN | EP_NO_Z) : PLAIN;
         if (epm != 0u) {
             if (p.st_nt == 512 && staged_lds_bytes_for<P, T, E, 512, 1>(true) <= max_lds())
                 return staged_go<P, T, VT, E, 512>(p, num_cus, s, epm);

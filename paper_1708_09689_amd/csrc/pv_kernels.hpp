@@ -108,6 +108,7 @@ struct SweepParams {
     const char* cg_src;
     int cg_dim, cg_halo, cg_sidew;   // cg_sidew: some offset has a y and a z step
     int cg_nocompile;   // take a generated kernel only if loaded (else the interpreted one)
+    int cg_series;      // a step of a series: the first one (gamma = 0) takes the later ones' instance
     int real_diag;      // the on-site block's diagonal is real
 };
 

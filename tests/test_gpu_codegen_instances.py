@@ -80,3 +80,19 @@ def test_complex64_blocks_off_16_bytes_share_the_instances(nb):
     pv.pv_cheb_series(lat, x, w, 9.0, 0.1, coef)
     assert pv.pv_codegen_instances() == n0 and torch.equal(y, w)
     assert bool((buf[:1] == 7.0).all()) and bool((buf[1 + n:] == 7.0).all())
+
+
+@pytest.mark.parametrize("K,instances", [(1, 1), (2, 2), (3, 2), (4, 2), (5, 2), (12, 3)])
+def test_instances_of_a_series(K, instances):
+    """Plain steps, accumulating steps, and the run-time epilogue of the first and
+    last accumulating ones: a long series compiles three."""
+    lat, x, _ = fresh_lattice(120 + K, torch.complex128)
+    y, w = torch.empty_like(x), torch.empty_like(x)
+    coef = np.random.default_rng(K).standard_normal(K + 1)
+    n0 = pv.pv_codegen_instances()
+    pv.pv_cheb_series(lat, x, y, 9.0, 0.1, coef)
+    assert pv.pv_codegen_instances() == n0 + instances
+    pv.pv_lattice_set_tuning(lat, pv.PV_C128, x.shape[1], {"kernel": 1})
+    pv.pv_lattice_set_codegen(lat, False)
+    pv.pv_cheb_series(lat, x, w, 9.0, 0.1, coef)
+    assert (y - w).abs().max() < 1e-12 * w.abs().max()
