@@ -661,8 +661,9 @@ int pv_codegen_instances(void);
  * to that step only.  cache_path names a JSON-lines file (NULL:
  * the PV_TUNE_CACHE environment variable, else no cache); an entry whose key
  * (stencil family, orbitals, extents, boundary conditions, nb, dtype, field
- * type, device architecture and CU count) matches is applied without timing,
- * and a new result is appended.  work: pv_autotune_workspace_size() bytes,
+ * type, device architecture and CU count, and the revision of the kernels that
+ * were timed) matches is applied without timing, and a new result is appended
+ * (an entry of another revision is not taken: the shapes are timed again).  work: pv_autotune_workspace_size() bytes,
  * overwritten.  Synchronises the stream.  out and ms (either may be NULL)
  * receive the chosen shape and its time per step in milliseconds (0 when
  * the shape came from the cache).

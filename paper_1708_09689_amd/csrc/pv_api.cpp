@@ -1559,6 +1559,11 @@ pv_status check_tuning(int dtype, const pv_tuning& t) {
     return PV_OK;
 }
 
+// Counts what the autotuner times: shapes found for other kernels are not
+// taken from a cache file.  1 (no "rev" in the key): one column per complex64
+// element, four dots per step, an accumulator in every series step.
+constexpr int kTuneRevision = 2;
+
 std::string tune_key(const pv_lattice* l, int dtype, int nb) {
     int dev = 0;
     hipDeviceProp_t prop{};
@@ -1584,10 +1589,11 @@ std::string tune_key(const pv_lattice* l, int dtype, int nb) {
     }
     char buf[512];
     std::snprintf(buf, sizeof buf,
-                  "family=%d orb=%d L=%lldx%lldx%lld bc=%d%d%d nb=%d dtype=%d vtype=%d dev=%s cus=%d stencil=%016llx",
+                  "family=%d orb=%d L=%lldx%lldx%lld bc=%d%d%d nb=%d dtype=%d vtype=%d dev=%s cus=%d "
+                  "stencil=%016llx rev=%d",
                   l->family, l->n_orb, (long long)l->L[0], (long long)l->L[1], (long long)l->L[2], l->periodic[0],
                   l->periodic[1], l->periodic[2], nb, dtype, l->rng_on ? 2 : (l->V ? l->vtype : -1), arch.c_str(), cus,
-                  gh);
+                  gh, kTuneRevision);
     return buf;
 }
 
