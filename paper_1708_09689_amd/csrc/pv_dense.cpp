@@ -71,7 +71,7 @@ void heev_jacobi(int n, std::vector<cd>& A, std::vector<double>& w, std::vector<
     // two passes over contiguous rows; A is Hermitian, so the rows give the
     // columns and the diagonal has closed forms.  A random 64 x 64: 29 ms with
     // std::complex rows and columns, 7.8 so (2.7 GHz, one core).
-    const size_t ld = size_t(n) + 9;   // odd: a column's entries spread over the cache
+    const size_t ld = (size_t(n) + 8) | 1;   // odd: a column's entries spread over the cache
     std::vector<double> ar(n * ld), ai(n * ld), vr(n * ld, 0.0), vi(n * ld, 0.0);
     double scale = 0.0;
     for (int i = 0; i < n; ++i) {
