@@ -46,9 +46,13 @@
  * field); the outputs are then not written.
  * Workspace.  Functions that need scratch device memory take (work,
  * work_bytes) from the caller; the matching *_workspace_size() call gives the
- * minimum size.  Too small a workspace gives PV_ERR_WORKSPACE.
+ * size for full speed with the lattice's field and launch shape as they are at
+ * the query.  It is also the least size, except for pv_kpm_moments,
+ * pv_cheb_series, pv_cheb_propagate and pv_batch_kpm_moments, which say what
+ * they accept; below the least size they give PV_ERR_WORKSPACE.
  * Determinism.  Reductions use fixed-order two-pass sums (no floating-point
- * atomics): repeated calls with the same inputs give bitwise equal results.
+ * atomics): repeated calls with the same inputs, launch shapes and work_bytes
+ * give bitwise equal results.
  * Threads.  Calls from several host threads may run at once on different
  * objects, or on one lattice or batch when none of them changes it
  * (set_potential, set_random_potential, set_tuning, autotune and the batch
@@ -254,7 +258,9 @@ pv_status pv_spmmv(pv_lattice *lat, int dtype, int nb, const void *x, const void
  *   - Generic stencils (generated kernels, see pv_lattice_set_codegen) take
  *     a generated kernel only when an earlier call on this GPU loaded that
  *     instance, else the interpreted generic kernel: compiling and loading
- *     one allocates.
+ *     one allocates.  With dots that is the instance of pv_spmmv with dots and
+ *     of pv_kpm_moments, without dots that of pv_spmmv with the same gamma
+ *     (zero or not), of the same dtype, nb > 1 or not, and launch shape.
  */
 #define PV_NOALLOC_SCRATCH_BYTES (64 << 20)
 pv_status pv_spmmv_noalloc(pv_lattice *lat, int dtype, int nb, const void *x, const void *z, void *y,
@@ -304,9 +310,16 @@ pv_status pv_random_block(pv_lattice *lat, int dtype, int nb, uint64_t seed, int
 /*
  * KPM moments (Sec. 2.2 DOS, Sec. 4): for every column c of the start block r
  *     mu[c][n] = Re <r_c, T_n(H~) r_c> / D,  H~ = (H - b)/a,  n = 0..M-1,
- * with D = n_rows, formed from M/2 fused sweeps through
+ * with D = n_rows, formed from M/2 fused steps through
  * mu_{2n} = 2<w_n,w_n>/D - mu_0 and mu_{2n+1} = 2 Re<w_n,w_{n+1}>/D - mu_1.
+ * A step is one sweep; on 2D graphene lattices of up to 4 complex128 columns
+ * several steps run in one pass where that is faster.
  * M even, 2 <= M <= 65536; a > 0.  r is read only.  mu: device [nb][M] FP64.
+ * Workspace: two blocks and up to 64 MiB for the partial dots of up to 64 steps,
+ * which one launch reduces (passes: four blocks).  Less is accepted down to two
+ * blocks, each rounded up to 256 bytes, and the partial dots of two steps (two
+ * times pv_spmmv_workspace_size holds them): then the steps run as sweeps and
+ * fewer are reduced at once; the moments agree up to rounding.
  */
 size_t pv_kpm_workspace_size(const pv_lattice *lat, int dtype, int nb, int M);
 pv_status pv_kpm_moments(pv_lattice *lat, int dtype, int nb, int M, double a, double b,
@@ -343,8 +356,11 @@ pv_status pv_kpm_spectral_function(int nb, int M, const double *mu, double a, do
 /*
  * Chebyshev series applied to a block (Sec. 4.1 and 4.2):
  *     Y = sum_{k=0}^{K} coef[k] T_k(H~) X,   coef: host complex [K+1] (re, im)
- * using K fused sweeps whose epilogue accumulates coef[k] * w_k.  X and Y
- * must not overlap.  K >= 0.
+ * using K fused sweeps, every third of which accumulates the terms of the three
+ * vectors that it holds, or on 2D graphene lattices of up to 4 columns, where that
+ * is faster, passes of several steps.  X and Y must not overlap.  K >= 0.
+ * Workspace: two blocks (each rounded up to 256 bytes), four for passes; with
+ * two the steps run as sweeps and the result agrees up to rounding.
  */
 size_t pv_cheb_series_workspace_size(const pv_lattice *lat, int dtype, int nb);
 pv_status pv_cheb_series(pv_lattice *lat, int dtype, int nb, double a, double b, int K,
@@ -355,7 +371,8 @@ pv_status pv_cheb_series(pv_lattice *lat, int dtype, int nb, double a, double b,
  * Chebyshev time propagation, Sec. 4.1 Eq. (U_1): nsteps steps of
  *     psi <- exp(-i b dt) [c_0 + 2 sum_{k=1}^{M} c_k T_k(H~)] psi,
  *     c_k = (-i)^k J_k(a dt)   (Bessel J_k by Miller's backward recurrence)
- * in place on psi (device [rows][nb]).  M >= 1, nsteps >= 0.
+ * in place on psi (device [rows][nb]).  M >= 1, nsteps >= 0.  Steps and
+ * workspace as for pv_cheb_series, with one block more.
  */
 size_t pv_cheb_propagate_workspace_size(const pv_lattice *lat, int dtype, int nb);
 pv_status pv_cheb_propagate(pv_lattice *lat, int dtype, int nb, double a, double b, double dt,
@@ -477,7 +494,8 @@ pv_status pv_kpm_moments_vjp(pv_lattice *lat, int dtype, int nb, int M, double a
 /*
  * The same gradient split in two calls for a caller that needs the moments
  * before the cotangent is known (reverse-mode autodiff):
- * pv_kpm_moments_ckpt computes mu exactly as pv_kpm_moments does and writes
+ * pv_kpm_moments_ckpt computes mu as pv_kpm_moments does (in sweeps, so on 2D
+ * lattices where that runs passes the two agree up to rounding) and writes
  * the checkpoint pairs (w_{jC}, w_{jC+1}) into `work` as it goes (sized by
  * pv_kpm_vjp_workspace_size, with the same ckpt_every);
  * pv_kpm_moments_vjp_ckpt then runs only the segment recomputation and the
@@ -531,15 +549,17 @@ pv_status pv_cheb_propagate_vjp_keep(pv_lattice *lat, int dtype, int nb, double 
  * Batched KPM over independent lattices (disorder realisations, possibly of
  * different sizes) of one stencil family: every Chebyshev step of all
  * instances is ONE kernel launch (each workgroup serves one instance, argument
- * records in a device table) followed by one per-instance fixed-order
- * reduction; the M/2 steps are captured into a HIP graph on the first call and
+ * records in a device table), and one more reduces the moments of up to 64 steps
+ * of every instance in a fixed order; the M/2 steps are captured into a HIP graph on the first call and
  * replayed on later calls with identical arguments (r pointers, a, b, fields,
  * workspace); the graph writes the moments into the workspace and each call
  * then copies them to mu, so mu may differ between calls.  Per instance i: mu[i][c][n] = Re <r_i,c, T_n(H~_i) r_i,c> / D_i,
  * H~_i = (H_i - b[i]) / a[i].  r: host array of n device pointers; mu: device
  * [n][nb][M].  The library owns the lattice list (borrowed lattices must
  * outlive the batch) and the graph; the workspace holds the argument tables,
- * so it must stay allocated while the graph may be replayed.
+ * so it must stay allocated while the graph may be replayed.  A workspace
+ * smaller than the query's is accepted as long as it holds two of the up to 64
+ * steps' partial dots, which come last: fewer steps are reduced at once.
  */
 pv_status pv_batch_create(int n, pv_lattice *const *lats, pv_batch **out);
 void pv_batch_destroy(pv_batch *batch);
@@ -608,6 +628,10 @@ typedef struct pv_tuning {
 /* Set (t != NULL) or reset to defaults (t == NULL) the shape used for
  * (dtype, nb), by every sweep including series steps (this drops a series
  * shape the autotuner chose); get returns the shape of the Chebyshev step.
+ * The shape is that of a sweep: while one with kernel != 0 is set, 2D lattices
+ * run sweeps only, no passes of several steps (pv_autotune's own choice leaves
+ * passes on; its result set here by hand, for instance from a file of the
+ * caller's, does not -- let pv_autotune read it from its cache file instead).
  * PV_ERR_INVALID_ARG for values outside the ranges above. */
 pv_status pv_lattice_set_tuning(pv_lattice *lat, int dtype, int nb, const pv_tuning *t);
 pv_status pv_lattice_get_tuning(const pv_lattice *lat, int dtype, int nb, pv_tuning *t);
@@ -620,8 +644,8 @@ pv_status pv_lattice_get_tuning(const pv_lattice *lat, int dtype, int nb, pv_tun
  * and, for every block entry, whether it is zero, real, imaginary or complex
  * -- and its sweeps take the built-in families' staged and direct kernels
  * instantiated for that pattern, compiled with hipRTC for the current
- * device on the first launch that needs an instance (about a second each;
- * the code objects stay loaded until the process ends, and PV_CODEGEN_CACHE
+ * device on the first launch that needs an instance (about 0.3 s each; a
+ * series needs up to three, moments and sweeps with dots share one; the code objects stay loaded until the process ends, and PV_CODEGEN_CACHE
  * may name a directory that keeps them across processes).  Compile on a
  * launch outside stream capture first: compilation is not a stream operation.
  * Results equal the interpreted generic kernels' up to the summation order

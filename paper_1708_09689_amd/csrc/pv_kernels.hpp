@@ -162,8 +162,9 @@ hipError_t launch_plane(const SweepParams& p, int TS, const PlanePass& q, hipStr
 // Fixed-order sums of [grid][nb][4] partials: dots[c][0..3].
 hipError_t launch_reduce_dots(const double* partials, int grid, int nb, double* dots, hipStream_t s);
 // Moments of the KPM steps n0 .. n0 + steps - 1 from their sweeps' partials,
-// step s at partials + s * stride, [grid][nb][width] (width 4 or 2: <w,w> and
-// Re <w,w'> come first), summed in a fixed order:
+// step s at partials + s * stride, [grid][nb][width] (<w,w> and Re <w,w'> come
+// first; width 4 where the stencil has a generated kernel, whose moment steps and
+// sweeps with dots share an instance, else 2), summed in a fixed order:
 //   n = 0: mu[c][0] = xx / D, mu[c][1] = xy / D
 //   else:  mu[c][2n] = 2 xx / D - mu[c][0], mu[c][2n+1] = 2 xy / D - mu[c][1]
 hipError_t launch_kpm_reduce(const double* partials, int64_t stride, int grid, int nb, int width, int n0, int steps,

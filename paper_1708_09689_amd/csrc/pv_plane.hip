@@ -18,9 +18,10 @@
 // accumulator has no halo and is updated in place).
 //
 // Measured: a propagation step of 64 terms on graphene 1024 x 1024 (complex128)
-// 1994 -> 594 us, 54 us per pass of six steps against 32 us per step; what
-// bounds a pass is the wave's own instructions (about 900 cycles per row, one
-// wave per SIMD) beside the 208 MB it moves.  Bounding the registers at 256
+// 2000 -> 614 us, 56 us per pass of six steps against 31 us per step.  What
+// bounds a pass is the wave's own instructions (one wave per SIMD, 1.4 us per row
+// of six levels, of which 33 are computed for 21) more than the 208 MB it moves:
+// 55 us with vectors of zeros.  Bounding the registers at 256
 // for two waves spills: 12 us per step instead of 8.6 (four steps per pass).
 #include "pv_sweep.hpp"
 
@@ -60,7 +61,8 @@ struct PlaneArgs {
 };
 
 // Value of the lane nb lanes below (UP) or above (any value where there is
-// none: such lanes' results reach the halo only); ONE: nb = 1, a data-parallel move instead of a permutation.
+// none: such lanes' results reach the halo only); ONE: nb = 1, a data-parallel
+// move instead of a permutation.
 template <bool UP, bool ONE>
 __device__ __forceinline__ int lane_shift(int v, int nb) {
     if constexpr (ONE) return __builtin_amdgcn_mov_dpp(v, UP ? 0x138 : 0x130, 0xf, 0xf, true);
@@ -78,10 +80,9 @@ __device__ __forceinline__ double lane_shift(double v, int nb) {
 // Raw buffers over a whole vector (below 2 GiB): a lane offset of kNone, or any
 // offset into a buffer of length 0, loads zeros and stores nothing (2^31 is past
 // every length, and neither the words of a chunk nor a row's offset carry it
-// round to the start).  So lanes and rows
-// outside the lattice, halo lanes and absent operands need no branches, and with
-// no memory operation in a branch the compiler waits for exactly the loads that
-// an iteration uses.
+// round to the start).  So lanes and rows outside the lattice, halo lanes and
+// absent operands need no branches, and with no memory operation in a branch the
+// compiler waits for exactly the loads that an iteration uses.
 constexpr uint32_t kNone = 0x80000000u;
 using Rsrc = __amdgpu_buffer_rsrc_t;
 struct Row {
@@ -399,9 +400,10 @@ int log2_of(int v) {
 
 // Tiles and walks of a pass of TS steps: one wave per SIMD of the 256 CUs (a
 // wave's registers leave room for no more), so walks as long as 256
-// workgroups of four allow (graphene 1024 x 1024, TS = 6: 21
-// rows per walk 44 us, 32 rows 54, and two rounds of shorter walks cost their
-// halos: 2048 x 2048 in 82 rows 196 us, in 40 rows 242).
+// workgroups of four allow.  us per pass of a series, graphene-2 complex128, TS =
+// 6: 1024 x 1024 in 21 rows per walk 56 (taken), 16 83, 32 69, 42 83; 2048 x 2048
+// in 82 rows 201 (taken), 40 263, 120 251: longer walks leave SIMDs idle, shorter
+// ones take two rounds and pay their halos twice.
 void plane_shape(const SweepParams& p, int TS, int& ntx, int& C, int& nyc, int& grid) {
     const int S = 64 / p.nb, own = S - 2 * TS;
     ntx = int((p.L[0] + own - 1) / own);
